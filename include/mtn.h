@@ -135,7 +135,9 @@ mtn_status mtn_pool_required_bytes(const mtn_pool_config *cfg, size_t *kv_bytes)
  * in the engine's paged pool; App. A: pinned sink blocks count against its
  * capacity).  Validates cfg, allocates the library's host state and its
  * device metadata and workspace (hipMalloc on the current device; the decode
- * split partials take max_sessions * Hq * 64 * (D + 2) floats), and takes
+ * split partials take max_sessions * Hq * 64 * (D + 2) floats, or, where that
+ * is more, what a split chunk prefill needs: at most 256 * CUs * (D + 2)
+ * floats, 34 MB on 256 CUs at D = 128), and takes
  * kv_dev (device, caller-owned, >= required bytes, 256-byte aligned) as the
  * pool.  The pool contents are not initialised.  *out receives the handle.
  * Errors: MTN_ERR_INVALID_ARG / MTN_ERR_UNSUPPORTED for cfg, MTN_ERR_DEVICE
@@ -342,10 +344,11 @@ mtn_status mtn_debug_poison_dead(mtn_pool *pool, void *stream);
 
 /* Tuning: query rows per chunk-prefill pass (rows are token x G + group head;
  * each pass of each kv head is one workgroup that reads the keys its rows can
- * see).  0 (the default) chooses per plan: 256, or 128 when the plan's 256-row
- * passes would occupy at most half the GPU's compute units; 128 or 256 fix it.
- * Takes effect at the next mtn_plan_begin.  Results are the same either way
- * up to fp32 summation order.  Other values: MTN_ERR_INVALID_ARG.            */
+ * see).  0 (the default) chooses per plan: 256, or 128 for the smallest
+ * batches; 128 or 256 fix it.  A plan whose passes leave compute units idle
+ * also cuts each pass's keys into segments, merged by log-sum-exp as the
+ * decode's are.  Takes effect at the next mtn_plan_begin.  Results are the
+ * same either way up to fp32 summation order.  Other values: MTN_ERR_INVALID_ARG.            */
 mtn_status mtn_pool_set_prefill_pass_rows(mtn_pool *pool, int32_t rows);
 
 /* Test / tuning: the decode kernel.  0 (default) chooses by shape; 1 forces

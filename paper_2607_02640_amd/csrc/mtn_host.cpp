@@ -17,6 +17,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 using namespace mtn;
@@ -24,6 +25,8 @@ using namespace mtn;
 namespace {
 
 constexpr int kStages = 4;  // pinned staging buffers in flight
+constexpr int kPfMinStages = 4;  // chunk prefill: stages (two blocks) of a key segment, at least
+constexpr int kPfMaxSplit = 16;  // ... and key segments of a pass, at most
 constexpr size_t kZeroPage = 2 * kBlock * 128 * 4;  // 16 KiB
 
 // Lowest-free-first block allocator over a bitmap (bit set = free).
@@ -98,6 +101,7 @@ struct mtn_pool {
     std::vector<int32_t> tok_sid, tok_pos, tok_row, tok_block, tok_off;
     std::vector<int32_t> upd_idx, upd_val;
     std::vector<int32_t> pf_items;  // prefill work records (kPfItem ints per row pass)
+    std::vector<std::pair<int32_t, int32_t>> pf_order;  // (keys, record) in launch order
     std::vector<int32_t> run_tok0, run_len;  // append runs: consecutive slots of one block
     std::vector<uint8_t> layer_done;
 
@@ -123,6 +127,7 @@ struct mtn_pool {
     int32_t n_cu = 0;              // compute units of the pool's device
     int32_t pf_rows_cfg = 0;       // chunk-prefill rows per pass: 0 = chosen per plan
     int32_t pf_rows = 0;           // ... of the open plan
+    int32_t pf_split = 1;          // chunk-prefill key segments of the open plan
     int32_t decode_kernel = 0;     // 0 automatic, 1 vector, 2 matrix (test / tuning hook)
     int32_t last_split = 0;        // key segments of the most recent decode launch
 
@@ -340,6 +345,85 @@ mtn_status launch_gate(mtn_pool *P) {
     return MTN_OK;
 }
 
+// Keys that the queries at positions [t0, t1] of a session see together.
+int64_t keys_seen(const mtn_pool *P, int64_t t0, int64_t t1) {
+    if (P->unbounded) return t1 + 1;
+    return std::min<int64_t>(P->S, t1 + 1) +
+           std::max<int64_t>(0, t1 - std::max<int64_t>(P->S, t0 - P->W + 1) + 1);
+}
+
+// The chunk prefill's launch: query rows per pass, key segments per pass, one
+// record per (sequence, row pass), longest first.
+//
+// A workgroup streams its keys at the pace of one CU, so a launch with fewer
+// workgroups than CUs leaves the rest idle: its passes' keys are then cut into
+// segments until the CUs are filled, at least kPfMinStages stages each and at
+// most kPfMaxSplit (more and the partial rows cost what the shorter segments
+// gain).  Per layer with the merge, one session of 25 tokens over 4100 keys
+// at G = 8 (4 passes of 256 rows or 8 of 128): 70.4 us unsplit, 27.9 at 4
+// segments, 19.1 at 16, 21.0 at 32; 16 sessions 73.4 us (128-row passes,
+// unsplit) against 47.7 (256-row, 4 segments); 32 fp8 sessions 117.0 against
+// 94.2 (256-row, 2 segments); one session over 600 keys 20.0 against 15.4 at
+// 4 segments and 17.3 at 2.
+// 128-row passes make more workgroups but read every key twice as often: they
+// pay only while the split cannot fill the CUs about twice over (one session
+// 19.1 against 22.3 us with 256, four 27.0 against 29.0; sixteen lose, 57.3
+// against 47.7).
+//
+// Longest first: with more workgroups than CUs the CUs that end early take the
+// next pass.  A 4100-token chunk's 516 causal passes in ascending order end
+// with the longest ones (measured per layer: 176 us; descending, 149 us).
+void plan_prefill(mtn_pool *P) {
+    const int32_t n_seq = P->n_seq;
+    const bool mfma = prefill_mfma_supported(P->cfg.kv_dtype, P->cfg.head_dim, P->G);
+    auto passes = [&](int64_t rpp) {
+        int64_t n = 0;
+        for (int32_t i = 0; i < n_seq; ++i) n += ceil_div((int64_t)P->seq_ntok[i] * P->G, rpp);
+        return n * P->cfg.n_kv_heads;
+    };
+    int64_t blocks = 0;  // of the longest sequence
+    for (int32_t i = 0; i < n_seq; ++i)
+        blocks = std::max(blocks, ceil_div(keys_seen(P, P->seq_pos0[i], P->seq_pos0[i] + P->seq_ntok[i] - 1),
+                                           kBlock));
+    const int64_t max_split = std::max<int64_t>(1, std::min<int64_t>(blocks / 2 / kPfMinStages, kPfMaxSplit));
+    int64_t rpp = P->pf_rows_cfg ? P->pf_rows_cfg : prefill_rows_per_pass();
+    if (!P->pf_rows_cfg && P->n_cu > 0 && prefill_pass_rows_valid(128) &&
+        2 * passes(rpp) <= P->n_cu && passes(128) * max_split <= 2 * (int64_t)P->n_cu)
+        rpp = 128;
+    P->pf_rows = (int32_t)rpp;
+    P->pf_split = 1;
+    if (mfma && P->n_cu > 0) {
+        const int64_t per = (int64_t)P->T * P->cfg.n_q_heads * (P->cfg.head_dim + 2);  // floats of a segment
+        const int64_t ns = std::min<int64_t>({P->n_cu / passes(rpp), max_split, (int64_t)P->part_floats / per});
+        P->pf_split = (int32_t)std::max<int64_t>(1, ns);
+    }
+    // one record per (sequence, row pass) with everything its workgroup
+    // needs before the first copy, so that it takes one metadata load.
+    // The prefill takes io row (row of t0) + j for token t0 + j: plans
+    // with an explicit row list (frame_step's decode rounds) carry one
+    // token per sequence and never reach it.
+    P->pf_items.clear();
+    P->pf_order.clear();
+    for (int32_t i = 0; i < n_seq; ++i) {
+        const int32_t t0 = P->seq_first[i], nt = P->seq_ntok[i];
+        const int64_t pos0 = P->seq_pos0[i];
+        for (int64_t p = 0; p * rpp < (int64_t)nt * P->G; ++p) {
+            const int64_t last = std::min<int64_t>((int64_t)nt * P->G, (p + 1) * rpp) - 1;
+            P->pf_order.emplace_back(
+                (int32_t)keys_seen(P, pos0 + p * rpp / P->G, pos0 + last / P->G),
+                (int32_t)P->pf_order.size());
+            const int32_t rec[kPfItem] = {(int32_t)p, t0, nt, P->seq_sid[i],
+                                          (int32_t)pos0, P->tok_row[t0], 0, 0};
+            P->pf_items.insert(P->pf_items.end(), rec, rec + kPfItem);
+        }
+    }
+    P->pf_one_pass = P->pf_order.size() == (size_t)n_seq;
+    if (P->n_cu > 0 && (int64_t)P->pf_order.size() * P->cfg.n_kv_heads > P->n_cu)
+        std::sort(P->pf_order.begin(), P->pf_order.end(), [](const auto &x, const auto &y) {
+            return x.first != y.first ? x.first > y.first : x.second < y.second;
+        });
+}
+
 // Internal plan begin.  rows == nullptr packs io rows in plan order.
 mtn_status plan_begin(mtn_pool *P, int32_t n_seq, const int32_t *sids, const int32_t *n_tok,
                       const int32_t *rows, void *stream) {
@@ -446,34 +530,9 @@ mtn_status plan_begin(mtn_pool *P, int32_t n_seq, const int32_t *sids, const int
                 P->run_len.push_back(1);
             }
         }
+    // one-token plans never reach the chunk prefill
     P->pf_items.clear();
-    {
-        // Rows per prefill pass.  Few sequences leave most CUs idle with full
-        // passes (one workgroup per sequence and kv head); then 128-row passes
-        // give each sequence more workgroups (each reading the keys its rows
-        // see), and a pass whose waves hold one tile skips the empty second.
-        int64_t rpp = P->pf_rows_cfg ? P->pf_rows_cfg : prefill_rows_per_pass();
-        if (!P->pf_rows_cfg && P->n_cu > 0) {
-            int64_t wgs = 0;
-            for (int32_t i = 0; i < n_seq; ++i) wgs += ceil_div((int64_t)n_tok[i] * P->G, rpp);
-            if (2 * wgs * P->cfg.n_kv_heads <= P->n_cu && prefill_pass_rows_valid(128)) rpp = 128;
-        }
-        P->pf_rows = (int32_t)rpp;
-        // one record per (sequence, row pass) with everything its workgroup
-        // needs before the first copy, so that it takes one metadata load.
-        // The prefill takes io row (row of t0) + j for token t0 + j: plans
-        // with an explicit row list (frame_step's decode rounds) carry one
-        // token per sequence and never reach it.
-        for (int32_t i = 0; i < n_seq; ++i) {
-            const int32_t t0 = P->seq_first[i];
-            for (int64_t p = 0; p * rpp < (int64_t)n_tok[i] * P->G; ++p) {
-                const int32_t rec[kPfItem] = {(int32_t)p, t0, n_tok[i], sids[i],
-                                              (int32_t)P->seq_pos0[i], P->tok_row[t0], 0, 0};
-                P->pf_items.insert(P->pf_items.end(), rec, rec + kPfItem);
-            }
-        }
-        P->pf_one_pass = P->pf_items.size() == (size_t)kPfItem * n_seq;
-    }
+    if (!P->all_single) plan_prefill(P);
     P->layer_done.assign((size_t)P->cfg.n_layers, 0);
     P->plan_open = true;
     P->plan_stream = stream;
@@ -496,7 +555,8 @@ mtn_status plan_begin(mtn_pool *P, int32_t n_seq, const int32_t *sids, const int
     put(P->upd_val.data(), U);
     const size_t o_items = (o + kPfItem - 1) / kPfItem * kPfItem;  // records 32-byte aligned
     while (o < o_items) h[o++] = 0;
-    put(P->pf_items.data(), (int32_t)P->pf_items.size());
+    if (!P->pf_items.empty())
+        for (const auto &it : P->pf_order) put(&P->pf_items[(size_t)it.second * kPfItem], kPfItem);
     const int32_t NR = (int32_t)P->run_tok0.size();
     put(P->run_tok0.data(), NR);
     put(P->run_len.data(), NR);
@@ -723,7 +783,8 @@ mtn_status decode_impl(mtn_pool *P, int32_t layer, const void *q, void *out, flo
 // no less than its append launch.
 bool prefill_fuses_append(const mtn_pool *P) {
     const int64_t wgs = (int64_t)(P->pf_items.size() / kPfItem) * P->cfg.n_kv_heads;
-    return !P->all_single && P->pf_one_pass && P->n_cu > 0 && wgs <= 2 * (int64_t)P->n_cu &&
+    return !P->all_single && P->pf_one_pass && P->pf_split == 1 && P->n_cu > 0 &&
+           wgs <= 2 * (int64_t)P->n_cu &&
            P->cfg.kv_dtype == MTN_FP8_E4M3 &&
            prefill_mfma_supported(P->cfg.kv_dtype, P->cfg.head_dim, P->G);
 }
@@ -740,7 +801,7 @@ mtn_status prefill_impl(mtn_pool *P, int32_t layer, const void *q, void *out, fl
         if (k_new) P->layer_done[layer] = 1;
         return MTN_OK;
     }
-    AttnArgs a = attn_args(P, layer, q, out, lse, 1);
+    AttnArgs a = attn_args(P, layer, q, out, lse, P->pf_split);
     a.k_new = k_new;
     a.v_new = v_new;
     hipEvent_t e0;
@@ -755,6 +816,13 @@ mtn_status prefill_impl(mtn_pool *P, int32_t layer, const void *q, void *out, fl
     st = timing_end(P, 1, e0, s);
     if (st) return st;
     if (k_new) P->layer_done[layer] = 1;
+    if (a.n_split > 1) {
+        st = timing_begin(P, s, &e0);
+        if (st) return st;
+        HIP_TRY(P, launch_merge(P->cfg.io_dtype, a, s));
+        st = timing_end(P, 3, e0, s);
+        if (st) return st;
+    }
     return MTN_OK;
 }
 
@@ -930,7 +998,9 @@ mtn_status pool_init(mtn_pool *P, const mtn_pool_config *cfg, void *kv_dev, void
     for (auto *v : {&P->tok_sid, &P->tok_pos, &P->tok_row, &P->tok_block, &P->tok_off, &P->upd_idx,
                     &P->upd_val, &P->run_tok0, &P->run_len})
         v->reserve((size_t)P->max_tok);
-    P->pf_items.reserve(kPfItem * ((size_t)P->max_tok * P->G / 128 + (size_t)cfg->max_sessions + 1));
+    const size_t max_items = (size_t)P->max_tok * P->G / 128 + (size_t)cfg->max_sessions + 1;
+    P->pf_items.reserve(kPfItem * max_items);
+    P->pf_order.reserve(max_items);
     P->layer_done.reserve((size_t)cfg->n_layers);
     if (!host_only) {
         auto bail = [&](hipError_t e, const char *w) {
@@ -969,22 +1039,28 @@ mtn_status pool_init(mtn_pool *P, const mtn_pool_config *cfg, void *kv_dev, void
         if ((e = hipMemcpy(P->d_inv_freq, inv.data(), sizeof(double) * half,
                            hipMemcpyHostToDevice)) != hipSuccess)
             return bail(e, "inv_freq upload");
-        // zero page: at least one whole (block, head) pair, K + V^T, at the
-        // largest element size and head dim
-        if ((e = hipMalloc(&P->d_zero, kZeroPage)) != hipSuccess) return bail(e, "zero page");
-        if ((e = hipMemsetAsync(P->d_zero, 0, kZeroPage, (hipStream_t)stream)) != hipSuccess)
-            return bail(e, "zero page clear");
-        P->part_floats = (size_t)cfg->max_sessions * cfg->n_q_heads * kMaxSplit * (cfg->head_dim + 2);
-        if ((e = hipMalloc(&P->d_part, sizeof(float) * P->part_floats)) != hipSuccess)
-            return bail(e, "partials");
-        if ((e = scratch_buffer(&P->d_scratch, &P->scratch_floats)) != hipSuccess)
-            return bail(e, "static scratch address");
         int dev = 0, n_cu = 0;
         if ((e = hipGetDevice(&dev)) != hipSuccess) return bail(e, "device");
         if ((e = hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev)) !=
             hipSuccess)
             return bail(e, "cu count");
         P->n_cu = n_cu;
+        // zero page: at least one whole (block, head) pair, K + V^T, at the
+        // largest element size and head dim
+        if ((e = hipMalloc(&P->d_zero, kZeroPage)) != hipSuccess) return bail(e, "zero page");
+        if ((e = hipMemsetAsync(P->d_zero, 0, kZeroPage, (hipStream_t)stream)) != hipSuccess)
+            return bail(e, "zero page clear");
+        // split partials: kMaxSplit segments of every query of a decode plan,
+        // or the segments of a chunk prefill that fill the CUs, one
+        // workgroup's rows each
+        P->part_floats =
+            std::max((size_t)cfg->max_sessions * cfg->n_q_heads * kMaxSplit,
+                     std::min((size_t)P->max_tok * cfg->n_q_heads * kMaxSplit,
+                              (size_t)n_cu * prefill_rows_per_pass())) * (cfg->head_dim + 2);
+        if ((e = hipMalloc(&P->d_part, sizeof(float) * P->part_floats)) != hipSuccess)
+            return bail(e, "partials");
+        if ((e = scratch_buffer(&P->d_scratch, &P->scratch_floats)) != hipSuccess)
+            return bail(e, "static scratch address");
         P->resident_units = count_resident_units(P);
         if ((e = hipEventCreateWithFlags(&P->order_ev, hipEventDisableTiming)) != hipSuccess)
             return bail(e, "event");

@@ -888,10 +888,15 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
     __shared__ __attribute__((aligned(16))) uint8_t bfs[F8 ? 2 : 1][F8 ? kPfStageBytes : 16];
     const AttnArgs &a = pa.a;
     const PoolGeom &g = a.g;
-    // one workgroup per (sequence, row pass, kv head): a long chunk's passes
-    // run in parallel, each over the keys its own rows can see
-    const int item = blockIdx.x / g.hkv;
-    const int kvh = blockIdx.x % g.hkv;
+    // one workgroup per (sequence, row pass, kv head, key segment): a long
+    // chunk's passes run in parallel, each over the keys its own rows can see,
+    // and a launch with few of them cuts each pass's keys into n_split
+    // segments of whole stages, whose partial results k_merge joins
+    const uint32_t ns = (uint32_t)a.n_split;
+    const uint32_t iu = blockIdx.x / ns;
+    const uint32_t seg = blockIdx.x - iu * ns;
+    const int item = (int)(iu / (uint32_t)g.hkv);
+    const int kvh = (int)(iu - (uint32_t)item * (uint32_t)g.hkv);
     // the pass's record: one scalar load before the union and the first copies
     const int32_t *rec = pa.items + (int64_t)item * kPfItem;
     const int pass = scalar_ld(rec, 0);
@@ -931,9 +936,16 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
     const int last_hi = ring_n > 0 ? (first_off + ring_n - 1) % kBlock + 1 : kBlock;
     const int ring_p0 = A - first_off;
     const int nvb = n_sb + n_rb;
-    const int n_stages = (nvb + 1) / 2;
+    // this segment's stages [st0, st0 + n_stages); from here on stages and
+    // virtual blocks count from the segment's first
+    const int all_stages = (nvb + 1) / 2;
+    const int st0 = seg_begin(seg, ns, all_stages);
+    const int n_stages = seg_begin(seg + 1, ns, all_stages) - st0;
+    const int vb0 = 2 * st0;
+    const int seg_nvb = min(nvb - vb0, 2 * n_stages);  // blocks of the segment
 
     auto vblock = [&](int v) {
+        v += vb0;
         PfBlock m;
         if (v < n_sb) {
             m.lb = v;
@@ -999,9 +1011,10 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
         rb = rb >= ring_blocks ? rb - ring_blocks : rb;
         return v < n_sb ? v : g.n_sink_blocks + rb;
     };
-    // physical block of virtual block v; -1 past the key union.  Every block
-    // of the union holds appended tokens, so the planner has assigned it.
-    auto phys = [&](int v) { return v < nvb ? scalar_ld(trow, vlb(v)) : -1; };
+    // physical block of virtual block v of the segment; -1 past it.  Every
+    // block of the key union holds appended tokens, so the planner has
+    // assigned it.
+    auto phys = [&](int v) { return v < seg_nvb ? scalar_ld(trow, vlb(v + vb0)) : -1; };
     // this wave's block of stage st into the stage's ring slot; stages past
     // the last (and absent blocks) move the zero page, so every stage costs
     // a DMA wave the same NPW instructions and its waits are constant
@@ -1276,7 +1289,7 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
         };
         // FULL stages: both blocks in the key union and inside the ring blocks
         // every row sees whole
-        const int full_r_lo = (fr_lo + 1) / 2, full_r_hi = min(fr_hi, nvb) / 2;
+        const int full_r_lo = (fr_lo + 1) / 2 - st0, full_r_hi = min(fr_hi, nvb) / 2 - st0;
         // V^T words of slots outside a block's valid range (they may hold
         // NaN, and 0 * NaN is NaN) are zeroed in registers: the lane's V
         // chunk holds slots lkey0 .. lkey0 + 7 of block lblk for one d, two
@@ -1536,7 +1549,7 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
         // every other stage (sinks, the window's left edge, the causal edge)
         // takes the masked step (exact for FULL stages too).  Three loops, so
         // each keeps its scores and accumulators in fixed registers.
-        const int st_a = min(full_r_lo, n_stages);
+        const int st_a = max(0, min(full_r_lo, n_stages));
         const int st_b = max(st_a, min(full_r_hi, n_stages));
         // NT: this wave's live tiles.  A wave whose second tile lies past the
         // pass's rows skips its MFMAs and exponentials; every wave still runs
@@ -1555,7 +1568,8 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
         // no DMA may land in LDS after the workgroup has ended
         if (dma_wave) vm_wait<0>();
 
-        // ---- epilogue: normalise and write rows of this pass
+        // ---- epilogue: normalise and write rows of this pass, or leave the
+        // segment's partial rows (a segment that a row sees nothing of: sum 0)
 #pragma unroll
         for (int i = 0; i < kPfTpw; ++i) {
             if (!live[i]) continue;
@@ -1564,6 +1578,18 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
             const int r = pass_row0 + (wv + kPfWaves * i) * 16 + ln16;
             if (r >= pass_end) continue;
             const int j = r / G, gh = r % G;
+            if (ns > 1) {
+                const int64_t th = (int64_t)(tok0 + j) * g.hq + hq0 + gh;
+                float *pa_ = a.part + (th * ns + seg) * D + 4 * lg;
+#pragma unroll
+                for (int dt = 0; dt < 8; ++dt)
+                    *(float4 *)(pa_ + dt * 16) =
+                        make_float4(acc[i][dt][0], acc[i][dt][1], acc[i][dt][2], acc[i][dt][3]);
+                if (lg == 0)
+                    *(float2 *)(a.part + (int64_t)a.p.n_tok * g.hq * ns * D + (th * ns + seg) * 2) =
+                        make_float2(m_ref[i], lt);
+                continue;
+            }
             const int64_t row = row_t0 + j;
             bf16_t *ob = (bf16_t *)a.out + (row * g.hq + hq0 + gh) * D;
             const float inv = 1.f / lt;
@@ -1740,10 +1766,13 @@ hipError_t launch_prefill_mfma(int dtype, const AttnArgs &a, const int32_t *item
         !prefill_pass_rows_valid(pass_rows))
         return hipErrorInvalidValue;
     if (((uintptr_t)items & 31) != 0) return hipErrorInvalidValue;  // records are 32-byte aligned
-    if ((a.k_new == nullptr) != (a.v_new == nullptr) || (a.k_new && dtype != 2))
-        return hipErrorInvalidValue;  // the fused append is the fp8 kernel's
+    if ((a.k_new == nullptr) != (a.v_new == nullptr) || (a.k_new && (dtype != 2 || a.n_split > 1)))
+        return hipErrorInvalidValue;  // the fused append is the unsplit fp8 kernel's
+    if (a.n_split < 1 || a.n_split > kMaxSplit) return hipErrorInvalidValue;
+    const int64_t wgs = (int64_t)n_items * a.g.hkv * a.n_split;
+    if (wgs > INT32_MAX) return hipErrorInvalidValue;
     PfArgs pa{a, items, zero_page, pass_rows};
-    dim3 grid((unsigned)(n_items * a.g.hkv)), block(64 * kPfWaves);
+    dim3 grid((unsigned)wgs), block(64 * kPfWaves);
     if (dtype == 2)
         launch_prefill_g<true>(G, grid, block, s, pa);
     else
