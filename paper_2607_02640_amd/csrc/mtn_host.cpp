@@ -695,20 +695,35 @@ int32_t count_resident_units(const mtn_pool *P) {
 }
 
 // Decode split heuristic.  A unit (query, kv head, segment) streams its keys
-// through an LDS ring whose pipeline fills at the start and drains at the
-// end, so units should be long, and a partly filled last round of units
-// leaves CUs idle.  So: if the unsplit units already fill the resident slots,
-// keep them whole; otherwise split just enough to fill one round, keeping at
-// least 16 blocks per segment.
+// through LDS rings, one per wave group, whose pipelines fill at the start and
+// drain at the end.  If the unsplit units already fill the resident slots they
+// stay whole.  Otherwise they are split to fill one round, as far as that
+// shortens the launch by more than the merge and its partials cost:
+//   - while the segments have a CU each, down to 2 blocks per wave group;
+//   - past that, to 5 per wave group with the vector kernel (up to eight
+//     one-wave workgroups share a CU), 8 with the matrix-core one.
+// Measured per layer with the merge (C++ launches back to back): fp32 G = 4,
+// 13 sessions x 57 blocks 36.1 us at 3 segments, 26.0 at 11; one G = 1 session
+// x 129 blocks 19.2 at 8, 14.7 at 25; bf16 D = 64, two G = 8 sessions x 95
+// blocks 15.0 at 5, 10.7 at 23; fp32 D = 64, 4 sessions x 9 blocks 13.1
+// unsplit, 9.7 at 5; 4 sessions G = 4 x 20 blocks 22.4 unsplit, 11.6 at 10;
+// matrix core: one G = 8 session x 257 blocks 13.3 at 16, 12.5 at 32; 8 fp8
+// sessions 16.7 at 16, 16.3 at 8.
+// A split that saves a wave group fewer than 4 blocks' time is not taken: the
+// merge costs about 2 us, a block about 0.6 (one session x 20 blocks, G = 8:
+// 10.0 us unsplit, 11.1 at 2).
 int32_t auto_split(const mtn_pool *P, int32_t n_items) {
-    int64_t units = (int64_t)n_items * P->cfg.n_kv_heads;
-    int64_t max_keys = P->unbounded ? P->cfg.max_len : (int64_t)P->S + P->W;
-    int64_t blocks = ceil_div(max_keys, kBlock) + 1;
-    int64_t resident = std::max<int32_t>(P->resident_units, 1);
+    const int64_t units = std::max<int64_t>((int64_t)n_items * P->cfg.n_kv_heads, 1);
+    const int64_t max_keys = P->unbounded ? P->cfg.max_len : (int64_t)P->S + P->W;
+    const int64_t resident = std::max<int32_t>(P->resident_units, 1);
     if (units >= resident) return 1;
-    int64_t sp = resident / std::max<int64_t>(units, 1);
-    sp = std::min<int64_t>(sp, std::max<int64_t>(1, blocks / 16));
-    return (int32_t)std::max<int64_t>(1, std::min<int64_t>(sp, kMaxSplit));
+    const bool mfma = P->cfg.kv_dtype == MTN_FP8_E4M3 || use_mfma_bf16(P);
+    const int64_t groups = mfma ? attn_mfma_groups(P->G) : attn_valu_groups(P->G);
+    const int64_t blocks = (ceil_div(max_keys, kBlock) + 1) / groups;  // of a wave group, unsplit
+    const int64_t fine = std::min<int64_t>(blocks / 2, P->n_cu / units);
+    const int64_t sp = std::min<int64_t>({resident / units, std::max<int64_t>(fine, blocks / (mfma ? 8 : 5)),
+                                          (int64_t)kMaxSplit});
+    return sp > 1 && blocks - blocks / sp >= 4 ? (int32_t)sp : 1;
 }
 
 // k_new / v_new non-null: the decode also appends the planned tokens of this

@@ -51,6 +51,8 @@ bool attn_valu_supported(int dtype, int d, int g) {
     return (dtype == 0 || dtype == 1) && (d == 64 || d == 128) && group_ok(g);
 }
 int attn_valu_resident_per_cu(int, int, int) { return 1; }
+int attn_valu_groups(int) { return 1; }
+int attn_mfma_groups(int) { return 4; }
 bool prefill_mfma_supported(int dtype, int d, int g) {
     return (dtype == 1 || dtype == 2) && d == 128 && group_ok(g);
 }

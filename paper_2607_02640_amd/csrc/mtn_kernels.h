@@ -120,6 +120,9 @@ hipError_t launch_attn_mfma_bf16(const AttnArgs &a, hipStream_t s);
 bool attn_valu_supported(int dtype, int d, int g);
 // workgroups of the vector attention kernel resident per CU (occupancy query)
 int attn_valu_resident_per_cu(int dtype, int d, int g);
+// wave groups that share a unit's keys in the vector and matrix-core decode
+int attn_valu_groups(int g);
+int attn_mfma_groups(int g);
 bool prefill_mfma_supported(int dtype, int d, int g);
 
 constexpr int kBlock = 16;      // tokens per KV block

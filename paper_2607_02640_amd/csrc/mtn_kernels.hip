@@ -1657,6 +1657,9 @@ int attn_valu_resident_per_cu(int dtype, int d, int g) {
     return d == 128 ? resident_d<float, 128>(g) : resident_d<float, 64>(g);
 }
 
+int attn_valu_groups(int g) { return g == 8 ? DecodeShape<8>::NG : DecodeShape<1>::NG; }
+static_assert(DecodeShape<1>::NG == DecodeShape<2>::NG && DecodeShape<2>::NG == DecodeShape<4>::NG, "");
+
 bool attn_valu_supported(int dtype, int d, int g) {
     if (g != 1 && g != 2 && g != 4 && g != 8) return false;
     if (d != 64 && d != 128) return false;

@@ -567,6 +567,11 @@ bool attn_fp8_supported(int d, int g) {
     return d == kF8D && (g == 1 || g == 2 || g == 4 || g == 8);
 }
 
+int attn_mfma_groups(int g) { return g == 8 ? MfmaShape<true, 8>::NG : MfmaShape<true, 4>::NG; }
+static_assert(MfmaShape<true, 1>::NG == MfmaShape<true, 4>::NG &&
+                  MfmaShape<true, 2>::NG == MfmaShape<true, 4>::NG &&
+                  MfmaShape<false, 8>::NG == MfmaShape<true, 8>::NG, "");
+
 int attn_fp8_resident_per_cu(int g) { return resident_mfma<true>(g); }
 
 bool attn_mfma_bf16_supported(int d, int g) { return attn_fp8_supported(d, g); }
