@@ -24,7 +24,12 @@ using namespace mtn;
 
 namespace {
 
-constexpr int kStages = 4;  // pinned staging buffers in flight
+constexpr int kStages = 4;  // pinned staging buffers of large plans in flight
+// Small plans: the plan kernel reads their metadata from the pinned buffer
+// itself (no copy command), kSmallSlots buffers of kSmallWords words, with one
+// event per half of them.
+constexpr int kSmallSlots = 16;
+constexpr int32_t kSmallWords = 2048;
 constexpr int kPfMinStages = 4;  // chunk prefill: stages (two blocks) of a key segment, at least
 constexpr int kPfMaxSplit = 16;  // ... and key segments of a pass, at most
 constexpr size_t kZeroPage = 2 * kBlock * 128 * 4;  // 16 KiB
@@ -120,6 +125,10 @@ struct mtn_pool {
     hipEvent_t stage_ev[kStages] = {};
     bool stage_used[kStages] = {};
     int stage_i = 0;
+    int32_t *h_small = nullptr;    // [kSmallSlots][kSmallWords]
+    hipEvent_t small_ev[2] = {};   // after the last plan of each half of the slots
+    bool small_used[2] = {};
+    int small_i = 0;
     PlanView view{};
     int32_t *d_pf_items = nullptr;
     int32_t *d_run_tok0 = nullptr, *d_run_len = nullptr;
@@ -458,12 +467,7 @@ mtn_status plan_begin(mtn_pool *P, int32_t n_seq, const int32_t *sids, const int
             need += new_blocks_needed(P, sids[i], P->len[sids[i]], n_tok[i], lbseen);
         if (need > P->alloc.n_free()) return fail(P, MTN_ERR_POOL_EXHAUSTED, "pool exhausted");
     }
-    int32_t *stage = nullptr;
     if (!P->host_only) {
-        // wait until the staging buffer we are about to overwrite was consumed
-        int si = P->stage_i;
-        if (P->stage_used[si]) HIP_TRY(P, hipEventSynchronize(P->stage_ev[si]));
-        stage = P->h_stage[si];
         if (P->have_last_stream && stream != P->last_stream) {
             HIP_TRY(P, hipEventRecord(P->order_ev, (hipStream_t)P->last_stream));
             HIP_TRY(P, hipStreamWaitEvent((hipStream_t)stream, P->order_ev, 0));
@@ -538,9 +542,28 @@ mtn_status plan_begin(mtn_pool *P, int32_t n_seq, const int32_t *sids, const int
     P->plan_stream = stream;
     if (P->host_only) return MTN_OK;
 
-    // ---- upload: one packed blob, then the apply kernel (table + RoPE)
+    // ---- upload: one packed blob and the plan kernel (table + RoPE), which
+    // takes a small blob from host memory itself
     const int32_t U = (int32_t)P->upd_idx.size();
-    int32_t *h = stage;
+    const int32_t NR = (int32_t)P->run_tok0.size();
+    const size_t o_items = ((size_t)5 * T + 2 * U + kPfItem - 1) / kPfItem * kPfItem;  // records 32-byte aligned
+    const size_t words = o_items + P->pf_items.size() + 2 * (size_t)NR;
+    const bool small = words <= (size_t)kSmallWords;
+    // a failed upload abandons the plan: the pool is as before the call
+    auto upload_fail = [&](hipError_t e, const char *where) {
+        plan_abort_impl(P);
+        return hip_fail(P, e, where);
+    };
+    // wait until the staging buffer we are about to overwrite was consumed
+    const int half = P->small_i / (kSmallSlots / 2);
+    bool &used = small ? P->small_used[half] : P->stage_used[P->stage_i];
+    const hipEvent_t ev = small ? P->small_ev[half] : P->stage_ev[P->stage_i];
+    hipError_t he = hipSuccess;
+    if (used && (!small || P->small_i % (kSmallSlots / 2) == 0)) {
+        he = hipEventSynchronize(ev);
+        if (he != hipSuccess) return upload_fail(he, "plan staging");
+    }
+    int32_t *const h = small ? P->h_small + (size_t)P->small_i * kSmallWords : P->h_stage[P->stage_i];
     size_t o = 0;
     auto put = [&](const int32_t *src, int32_t n) {
         std::memcpy(h + o, src, sizeof(int32_t) * (size_t)n);
@@ -553,26 +576,17 @@ mtn_status plan_begin(mtn_pool *P, int32_t n_seq, const int32_t *sids, const int
     put(P->tok_off.data(), T);
     put(P->upd_idx.data(), U);
     put(P->upd_val.data(), U);
-    const size_t o_items = (o + kPfItem - 1) / kPfItem * kPfItem;  // records 32-byte aligned
     while (o < o_items) h[o++] = 0;
     if (!P->pf_items.empty())
         for (const auto &it : P->pf_order) put(&P->pf_items[(size_t)it.second * kPfItem], kPfItem);
-    const int32_t NR = (int32_t)P->run_tok0.size();
     put(P->run_tok0.data(), NR);
     put(P->run_len.data(), NR);
     hipStream_t s = (hipStream_t)stream;
     int32_t *d = P->d_meta;
-    // a failed upload abandons the plan: the pool is as before the call
-    auto upload_fail = [&](hipError_t e, const char *where) {
-        plan_abort_impl(P);
-        return hip_fail(P, e, where);
-    };
-    hipError_t he = hipMemcpyAsync(d, h, o * sizeof(int32_t), hipMemcpyHostToDevice, s);
-    if (he != hipSuccess) return upload_fail(he, "plan upload");
-    he = hipEventRecord(P->stage_ev[P->stage_i], s);
-    if (he != hipSuccess) return upload_fail(he, "plan upload event");
-    P->stage_used[P->stage_i] = true;
-    P->stage_i = (P->stage_i + 1) % kStages;
+    if (!small) {
+        he = hipMemcpyAsync(d, h, o * sizeof(int32_t), hipMemcpyHostToDevice, s);
+        if (he != hipSuccess) return upload_fail(he, "plan upload");
+    }
     P->view.tok_sid = d;
     P->view.tok_pos = d + T;
     P->view.tok_row = d + 2 * T;
@@ -580,13 +594,29 @@ mtn_status plan_begin(mtn_pool *P, int32_t n_seq, const int32_t *sids, const int
     P->view.tok_off = d + 4 * T;
     P->view.rope = P->d_rope;
     P->view.n_tok = (int32_t)T;
-    const int32_t *d_upd_idx = d + 5 * T;
     P->d_pf_items = d + o_items;
     P->d_run_tok0 = P->d_pf_items + P->pf_items.size();
     P->d_run_len = P->d_run_tok0 + NR;
-    he = launch_plan_apply(d_upd_idx, d_upd_idx + U, U, P->d_table, P->view.tok_pos, (int32_t)T,
-                           P->d_inv_freq, P->cfg.head_dim / 2, P->d_rope, s);
+    const int32_t *from = small ? h : d;  // what the plan kernel reads
+    he = launch_plan_apply(small ? h : nullptr, d, (int32_t)o, from + 5 * T, from + 5 * T + U, U,
+                           P->d_table, from + T, (int32_t)T, P->d_inv_freq, P->cfg.head_dim / 2,
+                           P->d_rope, s);
     if (he != hipSuccess) return upload_fail(he, "launch_plan_apply");
+    // The buffer is free once the event after it has passed.  Plans of a pool
+    // run in order (also across streams), so one event covers every slot
+    // before it.
+    if (!small || P->small_i % (kSmallSlots / 2) == kSmallSlots / 2 - 1) {
+        he = hipEventRecord(ev, s);
+        if (he != hipSuccess) {
+            (void)hipStreamSynchronize(s);  // no event to wait for later
+            return upload_fail(he, "plan upload event");
+        }
+        used = true;
+    }
+    if (small)
+        P->small_i = (P->small_i + 1) % kSmallSlots;
+    else
+        P->stage_i = (P->stage_i + 1) % kStages;
     return MTN_OK;
 }
 
@@ -1043,6 +1073,12 @@ mtn_status pool_init(mtn_pool *P, const mtn_pool_config *cfg, void *kv_dev, void
             if ((e = hipEventCreateWithFlags(&P->stage_ev[i], hipEventDisableTiming)) != hipSuccess)
                 return bail(e, "event");
         }
+        if ((e = hipHostMalloc(&P->h_small, sizeof(int32_t) * kSmallSlots * kSmallWords,
+                               hipHostMallocDefault)) != hipSuccess)
+            return bail(e, "small stages");
+        for (auto &v : P->small_ev)
+            if ((e = hipEventCreateWithFlags(&v, hipEventDisableTiming)) != hipSuccess)
+                return bail(e, "event");
         size_t half = (size_t)cfg->head_dim / 2;
         if ((e = hipMalloc(&P->d_rope, sizeof(float2) * half * (size_t)P->max_tok)) != hipSuccess)
             return bail(e, "rope");
@@ -1103,6 +1139,9 @@ void mtn_pool_destroy(mtn_pool *P) {
             if (P->h_stage[i]) (void)hipHostFree(P->h_stage[i]);
             if (P->stage_ev[i]) (void)hipEventDestroy(P->stage_ev[i]);
         }
+        if (P->h_small) (void)hipHostFree(P->h_small);
+        for (auto &v : P->small_ev)
+            if (v) (void)hipEventDestroy(v);
         for (auto &v : P->ev_open)
             for (auto &pr : v) {
                 (void)hipEventDestroy(pr.a);

@@ -8,8 +8,9 @@
 
 namespace mtn {
 
-hipError_t launch_plan_apply(const int32_t *, const int32_t *, int32_t, int32_t *, const int32_t *,
-                             int32_t, const double *, int32_t, float2 *, hipStream_t) {
+hipError_t launch_plan_apply(const int32_t *, int32_t *, int32_t, const int32_t *, const int32_t *,
+                             int32_t, int32_t *, const int32_t *, int32_t, const double *, int32_t,
+                             float2 *, hipStream_t) {
     return hipErrorNotSupported;
 }
 hipError_t launch_append(int, const PoolGeom &, const PlanView &, int32_t, const void *,

@@ -52,7 +52,10 @@ struct AttnArgs {
 };
 
 // dtype codes match the public MTN_F32 / MTN_BF16 / MTN_FP8_E4M3
-hipError_t launch_plan_apply(const int32_t *upd_idx, const int32_t *upd_val, int32_t n_upd,
+// src non-null: pinned host words, first copied to dst (both 16-byte aligned,
+// whole 16-byte vectors allocated); the other arrays may lie in src.
+hipError_t launch_plan_apply(const int32_t *src, int32_t *dst, int32_t n_words,
+                             const int32_t *upd_idx, const int32_t *upd_val, int32_t n_upd,
                              int32_t *table, const int32_t *tok_pos, int32_t n_tok,
                              const double *inv_freq, int32_t half_d, float2 *rope,
                              hipStream_t s);
