@@ -55,7 +55,7 @@ int attn_valu_resident_per_cu(int, int, int) { return 1; }
 int attn_valu_groups(int) { return 1; }
 int attn_mfma_groups(int) { return 4; }
 bool prefill_mfma_supported(int dtype, int d, int g) {
-    return (dtype == 1 || dtype == 2) && d == 128 && group_ok(g);
+    return ((dtype == 1 && (d == 128 || d == 64)) || (dtype == 2 && d == 128)) && group_ok(g);
 }
 
 }  // namespace mtn

@@ -71,8 +71,8 @@ hipError_t launch_append(int dtype, const PoolGeom &g, const PlanView &p, int32_
 hipError_t launch_attn_valu(int dtype, const AttnArgs &a, hipStream_t s);
 hipError_t launch_merge(int dtype, const AttnArgs &a, hipStream_t s);
 
-// MFMA chunk-prefill attention (bf16 or fp8 pool, D = 128): one workgroup per (sequence,
-// row pass, kv head).  items: n_items records of kPfItem int32 (32-byte
+// MFMA chunk-prefill attention (bf16 pool, D = 128 or 64; fp8 pool, D = 128): one
+// workgroup per (sequence, row pass, kv head, key segment of a.n_split).  items: n_items records of kPfItem int32 (32-byte
 // aligned), one per row pass: {pass, first planned token t0, tokens, session
 // id, position of t0, io row of t0, 0, 0}; token t0 + j of the sequence uses
 // io row (row of t0) + j (multi-token plans always do); pass p covers the

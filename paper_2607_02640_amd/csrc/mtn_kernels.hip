@@ -761,8 +761,10 @@ __global__ __launch_bounds__(64 * kReadWaves) void k_read(const uint8_t *__restr
 }
 
 // ---------------------------------------------------------------------------
-// MFMA chunk prefill (bf16 or fp8 pool, D = 128): one workgroup per
-// (sequence, row pass, kv head)
+// MFMA chunk prefill (bf16 pool, D = 128 or 64; fp8 pool, D = 128): one
+// workgroup per (sequence, row pass, kv head, key segment).  (At D = 64 bf16 chunks the
+// vector kernel, which reads the window once per token, took 76 us a layer for
+// 21 sessions of 9 .. 33 tokens over 1500 keys at G = 8; this one 17 + 4.6.)
 // ---------------------------------------------------------------------------
 // Rows of the chunk are (token j, group head g) -> r = j * G + g, in tiles of
 // 16.  Keys stream in stages of 32 (two 16-token blocks) through LDS.
@@ -797,7 +799,6 @@ constexpr int kPfStages = MTN_PF_STAGES;        // LDS ring depth in stages of t
 #define MTN_PF_EARLY 3
 #endif
 constexpr int kPfEarly = MTN_PF_EARLY;          // ring stages copied before the query rotation
-constexpr int kPfStageBytes = 16384;
 
 struct PfArgs {
     AttnArgs a;
@@ -807,35 +808,41 @@ struct PfArgs {
 };
 
 // LDS layout of one stage: K tiles of blocks 0, 1 (the 16-byte chunks of a
-// key row permuted by kswz(b, key)), then V^T tiles (the two 16-byte halves of
+// key row permuted by swz_k(b, key)), then V^T tiles (the two 16-byte halves of
 // a d row swapped on bit 2 of d).  A K read instruction has lanes 0..15 on
-// keys {0..3, 8..11} (or {4..7, 12..15}) of both blocks; kswz gives those 16
-// (block, key) pairs 16 distinct chunk positions and ignores key bit 2, so
-// the second MFMA's rows sit exactly 4 rows (1 KiB) further.  Both patterns
-// read at the full LDS rate (measured: 228 and 240 B/clk/CU against 178 for
-// a swizzle without the block bit).
-__device__ __forceinline__ int kswz(int b, int key) {
-    return (key & 3) | ((key & 8) >> 1) | (b << 3);
-}
-__device__ __forceinline__ int lds_k(int b, int key, int chunk16) {
-    return b * 4096 + key * 256 + ((chunk16 ^ kswz(b, key)) << 4);
-}
-__device__ __forceinline__ int lds_v16(int b, int d, int half) {
-    return 8192 + b * 4096 + d * 32 + ((half ^ ((d >> 2) & 1)) << 4);
-}
-// Byte offset, inside a block's 8 KiB (K tile, V^T tile) pair, of the 16-byte
-// chunk that lands at stage byte offset `off`; *b = which block of the stage.
-__device__ __forceinline__ int stage_src(int off, int *b) {
-    if (off < 8192) {
-        *b = off >> 12;
-        const int r = off & 4095, key = r >> 8, pos = (r >> 4) & 15;
-        return key * 256 + ((pos ^ kswz(*b, key)) << 4);
+// keys {0..3, 8..11} (or {4..7, 12..15}) of both blocks; swz_k gives those 16
+// (block, key) pairs 16 distinct 16-byte columns of the banks -- 16 chunk
+// positions of a 256-byte row at D = 128, and at D = 64, where two 128-byte rows
+// share the banks' width, 8 positions for each parity of the key -- and ignores
+// key bit 2, so the second MFMA's rows sit exactly 4 rows further.  Both
+// patterns read at the full LDS rate (D = 128 measured: 228 and 240 B/clk/CU
+// against 178 for a swizzle without the block bit).
+template <int D>
+struct PfLds {
+    static constexpr int kTile = kBlock * D * 2;    // bytes of a K (or V^T) tile
+    static constexpr int kRow = D * 2;              // ... of a key row
+    static constexpr int kStage = 4 * kTile;        // ... of a stage
+    static __device__ __forceinline__ int swz_k(int b, int key) {
+        if constexpr (D == 128) return (key & 3) | ((key & 8) >> 1) | (b << 3);
+        return ((key & 2) >> 1) | ((key & 8) >> 2) | (b << 2);
     }
-    const int o2 = off - 8192;
-    *b = o2 >> 12;
-    const int r = o2 & 4095, d = r >> 5, pos = (r >> 4) & 1;
-    return 4096 + d * 32 + ((pos ^ ((d >> 2) & 1)) << 4);
-}
+    static __device__ __forceinline__ int k(int b, int key, int chunk16) {
+        return b * kTile + key * kRow + ((chunk16 ^ swz_k(b, key)) << 4);
+    }
+    static __device__ __forceinline__ int v16(int b, int d, int half) {
+        return 2 * kTile + b * kTile + d * 32 + ((half ^ ((d >> 2) & 1)) << 4);
+    }
+    // Byte offset, inside a block's (K tile, V^T tile) pair, of the 16-byte
+    // chunk that lands at stage byte offset `off`.
+    static __device__ __forceinline__ int src(int off) {
+        if (off < 2 * kTile) {
+            const int b = off / kTile, r = off % kTile, key = r / kRow, pos = (r % kRow) >> 4;
+            return key * kRow + ((pos ^ swz_k(b, key)) << 4);
+        }
+        const int r = off % kTile, d = r >> 5, pos = (r >> 4) & 1;
+        return kTile + d * 32 + ((pos ^ ((d >> 2) & 1)) << 4);
+    }
+};
 
 // A virtual block of a chunk's key union (sinks first, then the ring run):
 // logical block, valid slots [lo, hi), absolute position of slot 0.
@@ -862,7 +869,7 @@ __device__ __forceinline__ void f8_stage_to_bf16(const uint8_t *src, uint8_t *ds
             return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(
                                                     w, sk, decltype(hi)::value));
         };
-        *(uint4 *)(dst + lds_k(b, key, hc)) =
+        *(uint4 *)(dst + PfLds<kF8D>::k(b, key, hc)) =
             make_uint4(cv(c.x, std::false_type{}), cv(c.x, std::true_type{}),
                        cv(c.y, std::false_type{}), cv(c.y, std::true_type{}));
     }
@@ -878,7 +885,7 @@ __device__ __forceinline__ void f8_stage_to_bf16(const uint8_t *src, uint8_t *ds
         for (int x = 0; x < 2; ++x) {  // dim 2 dp + x: keys 4 kg .. 4 kg + 3
             const auto lo = __builtin_amdgcn_cvt_pk_f32_fp8(w[x], false);
             const auto hi = __builtin_amdgcn_cvt_pk_f32_fp8(w[x], true);
-            *(uint2 *)(dst + lds_v16(b, 2 * dp + x, kg >> 1) + (kg & 1) * 8) =
+            *(uint2 *)(dst + PfLds<kF8D>::v16(b, 2 * dp + x, kg >> 1) + (kg & 1) * 8) =
                 make_uint2(pack_bf16x2(lo[0] * sv[0], lo[1] * sv[1]),
                            pack_bf16x2(hi[0] * sv[2], hi[1] * sv[3]));
         }
@@ -889,14 +896,17 @@ __device__ __forceinline__ void f8_stage_to_bf16(const uint8_t *src, uint8_t *ds
 // regions (per block four 1 KiB DMA instructions plus the 32 exponent
 // bytes), and every stage is converted into one of two bf16 stage buffers (a
 // second barrier) before the same MFMA stage body runs on it.
-template <int G, bool F8>
+template <int D, int G, bool F8>
 __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
-    constexpr int D = 128;
-    constexpr int SB = F8 ? 2 * kF8Read : kPfStageBytes;  // bytes of a ring stage
+    using Lds = PfLds<D>;
+    static_assert(D == 128 || (D == 64 && !F8), "head dims with a stage layout");
+    constexpr int ND = D / 32;   // 32-wide slices of d (QK MFMAs per key row)
+    constexpr int NT16 = D / 16; // 16-wide tiles of d (PV MFMAs)
+    constexpr int SB = F8 ? 2 * kF8Read : Lds::kStage;  // bytes of a ring stage
     static_assert(kPfStages >= 3 && kPfStages <= 8, "ring depth (the DMA waits count at most 63)");
     static_assert(kPfEarly >= 1 && kPfEarly <= kPfStages - 1, "early stages are ring prologue stages");
     __shared__ __attribute__((aligned(16))) uint8_t ring[kPfStages][SB];
-    __shared__ __attribute__((aligned(16))) uint8_t bfs[F8 ? 2 : 1][F8 ? kPfStageBytes : 16];
+    __shared__ __attribute__((aligned(16))) uint8_t bfs[F8 ? 2 : 1][F8 ? Lds::kStage : 16];
     const AttnArgs &a = pa.a;
     const PoolGeom &g = a.g;
     // one workgroup per (sequence, row pass, kv head, key segment): a long
@@ -985,10 +995,11 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
     // block i & 1, the other waves only meet them at the barrier.  Lane
     // source offsets inside the block and the LDS offsets of the
     // instructions inside a ring slot are the same for every stage.  A block
-    // takes NDI instructions -- bf16: 4 for the K tile, 4 for the V^T tile;
+    // takes NDI instructions of 1 KiB -- bf16: half for the K tile, half for the V^T tile;
     // F8: 4 for the K and V codes, one 2-lane instruction for the 32 exponent
     // bytes -- and DMA wave i issues those k = (i >> 1) + (DW / 2) m, m < NPW.
-    constexpr int NDI = F8 ? 5 : 8;  // DMA instructions per block
+    constexpr int NKI = Lds::kTile / 1024;    // ... of a K (or V^T) tile
+    constexpr int NDI = F8 ? 5 : 2 * NKI;  // DMA instructions per block
     constexpr int DW = F8 ? 2 : MTN_PF_DMA_WAVES;
     constexpr int NPW = NDI / (DW / 2);  // DMA instructions per DMA wave per stage
     static_assert(DW >= 2 && NPW * (DW / 2) == NDI, "DMA split");
@@ -1010,9 +1021,9 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
             dsrc[m] = j < 4 ? j * 1024 + lane * 16 : kF8Exp + (lane & 1) * 16;
             ddst[m] = db * kF8Read + (j < 4 ? j * 1024 : kF8Exp);
         } else {
-            const int off = j < 4 ? db * 4096 + j * 1024 : 8192 + db * 4096 + (j - 4) * 1024;
-            int bb;
-            dsrc[m] = stage_src(off + lane * 16, &bb);
+            const int off = j < NKI ? db * Lds::kTile + j * 1024
+                                    : (2 + db) * Lds::kTile + (j - NKI) * 1024;
+            dsrc[m] = Lds::src(off + lane * 16);
             ddst[m] = off;
         }
     }
@@ -1051,17 +1062,17 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
 
     // per-lane LDS offsets inside a stage: K rows of the two QK MFMAs
     // (permuted keys), and the lane's V^T chunk
-    // (the two MFMAs' keys differ by 4, which kswz ignores: MFMA 1's row is
-    // MFMA 0's plus 4 * 256 bytes)
-    int koff[4];
+    // (the two MFMAs' keys differ by 4, which the swizzle ignores: MFMA 1's row is
+    // MFMA 0's plus 4 rows)
+    int koff[ND];
     {
         const int kap = 8 * (ln16 >> 2) + (ln16 & 3);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) koff[s] = lds_k(kap >> 4, kap & 15, s * 4 + lg);
+        for (int s = 0; s < ND; ++s) koff[s] = Lds::k(kap >> 4, kap & 15, s * 4 + lg);
     }
     const int lblk = lg >> 1;          // the block of this lane's eight keys
     const int lkey0 = 8 * (lg & 1);    // ... and the first of them
-    const int voff = lds_v16(lblk, ln16, lg & 1);  // + dt * 16 * 32 for d tile dt
+    const int voff = Lds::v16(lblk, ln16, lg & 1);  // + dt * 16 * 32 for d tile dt
 
     const int hq0 = kvh * G;
     // Fused chunk append (fp8 pool; a.k_new set).  The host passes it only
@@ -1153,8 +1164,8 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
             fr_hi = n_sb + max(uhi, ulo);
         }
         // ---- per-wave query tiles: rows r = pass_row0 + (wv + kPfWaves i) * 16 + ln16
-        uint4 qf[kPfTpw][4];
-        f32x4_t acc[kPfTpw][8];
+        uint4 qf[kPfTpw][ND];
+        f32x4_t acc[kPfTpw][NT16];
         // row reference max (log2 units) and the row sum of the probabilities.
         // bf16 pool: the sum of their bf16 roundings, accumulated by an MFMA
         // against all-ones (every entry = the row sum).  fp8 pool: ls holds
@@ -1186,8 +1197,8 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
         // pass record), then the arithmetic.  (Interleaved with the rotation,
         // with the io row loaded first, the loads took one memory round trip
         // per slice: about 10 us of every workgroup's prologue.)  Slices s and
-        // s + 2 share their (cos, sin) pairs (dims d and d + 64 hold one
-        // rotation pair).
+        // s + ND / 2 share their (cos, sin) pairs (dims d and d + D / 2 hold
+        // one rotation pair).
         int tq_j[kPfTpw], gh_i[kPfTpw];
         bool rv_i[kPfTpw];
         int64_t row_i[kPfTpw];
@@ -1208,10 +1219,10 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
             l_i[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             ls[i] = 0.f;
 #pragma unroll
-            for (int dt = 0; dt < 8; ++dt) acc[i][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int dt = 0; dt < NT16; ++dt) acc[i][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
         }
-        uint4 qx[kPfTpw][4], qy[kPfTpw][4];  // dims d0 .. d0 + 7 and their partners d0 ^ 64
-        float4 qc[kPfTpw][2][4];             // (cos, sin) of dims (d0 & 63) .. + 7
+        uint4 qx[kPfTpw][ND], qy[kPfTpw][ND];  // dims d0 .. d0 + 7 and their partners d0 ^ (D / 2)
+        float4 qc[kPfTpw][ND / 2][4];          // (cos, sin) of dims (d0 % (D / 2)) .. + 7
         AppBatch ab;
         if (fuse && !dma_wave) app_load(aw, ab);
         __builtin_amdgcn_sched_barrier(0);  // the query loads follow at once
@@ -1221,13 +1232,13 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
             const bf16_t *qh = (const bf16_t *)a.q + (row_i[i] * g.hq + hq0 + gh_i[i]) * D;
             const float2 *rp = a.p.rope + (int64_t)t * (D / 2);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < ND; ++s) {
                 const int d0 = s * 32 + 8 * lg;
                 qx[i][s] = *(const uint4 *)(qh + d0);
-                qy[i][s] = *(const uint4 *)(qh + (d0 ^ 64));
+                qy[i][s] = *(const uint4 *)(qh + (d0 ^ (D / 2)));
             }
 #pragma unroll
-            for (int h2 = 0; h2 < 2; ++h2)
+            for (int h2 = 0; h2 < ND / 2; ++h2)
 #pragma unroll
                 for (int k = 0; k < 4; ++k) qc[i][h2][k] = ((const float4 *)(rp + h2 * 32 + 8 * lg))[k];
         }
@@ -1244,21 +1255,21 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
 #pragma unroll
         for (int i = 0; i < kPfTpw; ++i) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                // dims d0 + e, e < 8, d0 = s*32 + 8*lg; RoPE partner is d +- 64
+            for (int s = 0; s < ND; ++s) {
+                // dims d0 + e, e < 8, d0 = s*32 + 8*lg; RoPE partner is d +- D / 2
                 const int d0 = s * 32 + 8 * lg;
                 float xv[8], yv[8], cs[16];
                 unpack8(qx[i][s], xv);
                 unpack8(qy[i][s], yv);
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    const float4 c = qc[i][s & 1][k];
+                    const float4 c = qc[i][s % (ND / 2)][k];
                     cs[4 * k] = c.x;
                     cs[4 * k + 1] = c.y;
                     cs[4 * k + 2] = c.z;
                     cs[4 * k + 3] = c.w;
                 }
-                const float sg = d0 < 64 ? -1.f : 1.f;
+                const float sg = d0 < D / 2 ? -1.f : 1.f;
                 // rows past the pass become zero queries; a mask rather than a
                 // select, so that the compiler keeps the loads unconditional
                 const uint32_t keep = rv_i[i] ? 0xFFFFFFFFu : 0u;
@@ -1349,9 +1360,9 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
                 sb[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             }
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < ND; ++s) {
                 const uint4 k0 = *(const uint4 *)(sm + koff[s]);
-                const uint4 k1 = *(const uint4 *)(sm + koff[s] + 1024);
+                const uint4 k1 = *(const uint4 *)(sm + koff[s] + 4 * Lds::kRow);
 #pragma unroll
                 for (int i = 0; i < NT; ++i) {
                     sa[i] = mfma16x16x32(k0, qf[i][s], sa[i]);
@@ -1412,15 +1423,15 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
             const uint8_t *sm = stage_buf(st);
             // V^T chunks of stage st (visible since the previous barrier):
             // their LDS latency overlaps the wait below
-            uint4 vf[8];
+            uint4 vf[NT16];
 #pragma unroll
-            for (int dt = 0; dt < 8; ++dt) vf[dt] = *(const uint4 *)(sm + voff + dt * 16 * 32);
+            for (int dt = 0; dt < NT16; ++dt) vf[dt] = *(const uint4 *)(sm + voff + dt * 16 * 32);
             if constexpr (MASKED) {
                 mask_scores(nt_c, st, sa, sb);
                 uint32_t vm[4];
                 v_slot_mask(st, vm);
 #pragma unroll
-                for (int dt = 0; dt < 8; ++dt)
+                for (int dt = 0; dt < NT16; ++dt)
                     vf[dt] = make_uint4(vf[dt].x & vm[0], vf[dt].y & vm[1], vf[dt].z & vm[2], vf[dt].w & vm[3]);
             }
             // stage st + 1 (ping-pong: st + 2) landed (zero-page stages after
@@ -1444,12 +1455,12 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
             // instructions then cover their LDS latency (2.7-7.5 % per layer);
             // fp8 measured no gain, its reads stay with the QK MFMAs
             const uint8_t *nsm = stage_buf(st + 1);
-            uint4 kf[4][2];
+            uint4 kf[ND][2];
             auto load_kf = [&]() __attribute__((always_inline)) {
 #pragma unroll
-                for (int s = 0; s < 4; ++s) {
+                for (int s = 0; s < ND; ++s) {
                     kf[s][0] = *(const uint4 *)(nsm + koff[s]);
-                    kf[s][1] = *(const uint4 *)(nsm + koff[s] + 1024);
+                    kf[s][1] = *(const uint4 *)(nsm + koff[s] + 4 * Lds::kRow);
                 }
             };
             if constexpr (!F8) load_kf();
@@ -1489,20 +1500,20 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
                     else
                         ls[i] *= alpha;
 #pragma unroll
-                    for (int dt = 0; dt < 8; ++dt) acc[i][dt] *= alpha;
+                    for (int dt = 0; dt < NT16; ++dt) acc[i][dt] *= alpha;
                 }
             }
             // QK of the next stage (at the last stage it reads a stale
             // buffer and its scores are dropped), interleaved with this
-            // stage's probabilities: in each of four groups, one MFMA then
-            // two VALU instructions, so the exponentials run while the matrix
+            // stage's probabilities: in each of ND groups, one MFMA then 8 / ND
+            // VALU instructions, so the exponentials run while the matrix
             // core works
             if constexpr (F8) load_kf();
             f32x4_t na[kPfTpw], nb[kPfTpw];
             float p[kPfTpw][8];
-            constexpr int kEpg = 2 * NT;  // probabilities per group
+            constexpr int kEpg = 8 * NT / ND;  // probabilities per group
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
+            for (int s = 0; s < ND; ++s) {
 #pragma unroll
                 for (int i = 0; i < NT; ++i) {
                     const f32x4_t c0 = kShift ? csh[i] : f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -1519,11 +1530,11 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
                     asm volatile("" : "+v"(p[i][e]));
                 }
 #ifndef MTN_PF_NO_SCHED
-                if (s == 0) __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);  // all K reads first
+                if (s == 0) __builtin_amdgcn_sched_group_barrier(0x100, 2 * ND, 0);  // all K reads first
 #pragma unroll
                 for (int k = 0; k < 2 * NT; ++k) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x402, 2, 0);  // VALU or TRANS
+                    __builtin_amdgcn_sched_group_barrier(0x402, 8 / ND, 0);  // VALU or TRANS
                 }
                 __builtin_amdgcn_sched_barrier(0);
 #endif
@@ -1546,7 +1557,7 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
                              ((p[i][4] + p[i][5]) + (p[i][6] + p[i][7]));
             }
 #pragma unroll
-            for (int dt = 0; dt < 8; ++dt) {
+            for (int dt = 0; dt < NT16; ++dt) {
 #pragma unroll
                 for (int i = 0; i < NT; ++i) acc[i][dt] = mfma16x16x32(vf[dt], pb[i], acc[i][dt]);
             }
@@ -1593,7 +1604,7 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
                 const int64_t th = (int64_t)(tok0 + j) * g.hq + hq0 + gh;
                 float *pa_ = a.part + (th * ns + seg) * D + 4 * lg;
 #pragma unroll
-                for (int dt = 0; dt < 8; ++dt)
+                for (int dt = 0; dt < NT16; ++dt)
                     *(float4 *)(pa_ + dt * 16) =
                         make_float4(acc[i][dt][0], acc[i][dt][1], acc[i][dt][2], acc[i][dt][3]);
                 if (lg == 0)
@@ -1605,7 +1616,7 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
             bf16_t *ob = (bf16_t *)a.out + (row * g.hq + hq0 + gh) * D;
             const float inv = 1.f / lt;
 #pragma unroll
-            for (int dt = 0; dt < 8; ++dt) {
+            for (int dt = 0; dt < NT16; ++dt) {
                 const int d0 = dt * 16 + 4 * lg;
                 uint2 w = make_uint2(pack_bf16x2(acc[i][dt][0] * inv, acc[i][dt][1] * inv),
                                      pack_bf16x2(acc[i][dt][2] * inv, acc[i][dt][3] * inv));
@@ -1678,7 +1689,7 @@ bool attn_valu_supported(int dtype, int d, int g) {
 }
 
 bool prefill_mfma_supported(int dtype, int d, int g) {
-    return (dtype == 1 || dtype == 2) && d == 128 && (g == 1 || g == 2 || g == 4 || g == 8);
+    return ((dtype == 1 && (d == 128 || d == 64)) || (dtype == 2 && d == 128)) && (g == 1 || g == 2 || g == 4 || g == 8);
 }
 
 hipError_t launch_plan_apply(const int32_t *src, int32_t *dst, int32_t n_words,
@@ -1768,13 +1779,13 @@ int prefill_rows_per_pass() { return kPfRowsPerPass; }
 // tile per wave) or the full kPfRowsPerPass
 bool prefill_pass_rows_valid(int rows) { return rows == kPfRowsPerPass || rows == kPfWaves * 16; }
 
-template <bool F8>
+template <int D, bool F8>
 void launch_prefill_g(int G, dim3 grid, dim3 block, hipStream_t s, const PfArgs &pa) {
     switch (G) {
-        case 1: hipLaunchKernelGGL((k_prefill_mfma<1, F8>), grid, block, 0, s, pa); break;
-        case 2: hipLaunchKernelGGL((k_prefill_mfma<2, F8>), grid, block, 0, s, pa); break;
-        case 4: hipLaunchKernelGGL((k_prefill_mfma<4, F8>), grid, block, 0, s, pa); break;
-        default: hipLaunchKernelGGL((k_prefill_mfma<8, F8>), grid, block, 0, s, pa); break;
+        case 1: hipLaunchKernelGGL((k_prefill_mfma<D, 1, F8>), grid, block, 0, s, pa); break;
+        case 2: hipLaunchKernelGGL((k_prefill_mfma<D, 2, F8>), grid, block, 0, s, pa); break;
+        case 4: hipLaunchKernelGGL((k_prefill_mfma<D, 4, F8>), grid, block, 0, s, pa); break;
+        default: hipLaunchKernelGGL((k_prefill_mfma<D, 8, F8>), grid, block, 0, s, pa); break;
     }
 }
 
@@ -1793,9 +1804,11 @@ hipError_t launch_prefill_mfma(int dtype, const AttnArgs &a, const int32_t *item
     PfArgs pa{a, items, zero_page, pass_rows};
     dim3 grid((unsigned)wgs), block(64 * kPfWaves);
     if (dtype == 2)
-        launch_prefill_g<true>(G, grid, block, s, pa);
+        launch_prefill_g<128, true>(G, grid, block, s, pa);
+    else if (a.g.d == 128)
+        launch_prefill_g<128, false>(G, grid, block, s, pa);
     else
-        launch_prefill_g<false>(G, grid, block, s, pa);
+        launch_prefill_g<64, false>(G, grid, block, s, pa);
     return hipGetLastError();
 }
 

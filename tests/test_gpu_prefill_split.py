@@ -12,8 +12,8 @@ from tests._gpu_util import Harness, make_pool, say
 pytestmark = pytest.mark.gpu
 
 
-def _setup(dtype, hq, hkv, S, W, cmax, n, L=1):
-    kw = dict(n_layers=L, hq=hq, hkv=hkv, d=128, S=S, W=W, dtype=dtype)
+def _setup(dtype, hq, hkv, S, W, cmax, n, L=1, d=128):
+    kw = dict(n_layers=L, hq=hq, hkv=hkv, d=d, S=S, W=W, dtype=dtype)
     blocks = n * (-(-S // 16) + -(-(W + cmax - 1) // 16)) if W else n * 48
     pool = make_pool(**kw, cmax=cmax, max_sessions=n, n_blocks=blocks, max_len=0 if W else 760)
     return pool, Harness(pool, n_sessions=n, **kw)
@@ -27,6 +27,9 @@ def _setup(dtype, hq, hkv, S, W, cmax, n, L=1):
     ("bf16", 8, 4, None, 0),     # unbounded: segments grow with the session
     ("fp8", 8, 4, 520, 0),
     ("fp8", 2, 17, 400, 256),
+    ("bf16-d64", 8, 4, 520, 0),  # head dim 64: half the slices, another LDS swizzle
+    ("bf16-d64", 2, 20, None, 256),
+    ("bf16-d64", 1, 0, 390, 128),
 ])
 def test_split_prefill_matches_oracle(dtype, g, S, W, rows):
     """Two sessions of very different lengths in one plan: the short one has
@@ -34,7 +37,8 @@ def test_split_prefill_matches_oracle(dtype, g, S, W, rows):
     and log-sum-exps are checked from an empty pool on, so the number of
     segments runs from one to the largest this window gives."""
     say(f"split prefill {dtype} G={g} S={S} W={W} rows={rows}")
-    pool, h = _setup(dtype, 2 * g, 2, S, W, 60, 2)
+    dtype, _, d64 = dtype.partition("-")
+    pool, h = _setup(dtype, 2 * g, 2, S, W, 60, 2, d=64 if d64 else 128)
     if rows:
         pool.set_prefill_pass_rows(rows)
     pool.set_timing(True)
