@@ -25,6 +25,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace mtn {
 namespace {
@@ -115,7 +116,6 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
     constexpr int BLK = F8 ? kF8Read : 2 * kBlock * D * 2;
     // DMA instructions per block: 4 x 1 KiB + the 32 exponent bytes, or 8 x 1 KiB
     constexpr int NIW = F8 ? 5 : 8;
-    constexpr int ESZ = F8 ? 1 : 2;  // bytes per stored element
     static_assert(G >= 1 && G <= 16, "heads per kv group");
     static_assert(NBUF >= 2 && NBUF <= 8, "ring depth");
     static_assert(NBUF * BLK >= 16 * D * 4, "merge scratch fits one wave's ring");
@@ -148,26 +148,37 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
     const int32_t *trow = g.table + (int64_t)sid * g.row_len;
     const uint32_t ring0 = lds_addr(&ring[wv][0][0]);
 
-    BlockIter it_issue(g, vr, v0), it_proc(g, vr, v0);
-    auto issue = [&](int i) {
-        int lb, lo, hi;
-        it_issue.get(&lb, &lo, &hi);
-        it_issue.next();
-        int phys = scalar_ld(trow, __builtin_amdgcn_readfirstlane(lb));
-        phys = phys < 0 ? 0 : phys;  // unassigned: any valid block, every slot masked
-        const uint8_t *src = head_base + (int64_t)phys * g.block_stride;
-        const uint32_t dst = ring0 + (uint32_t)((i % NBUF) * BLK);
-        if constexpr (F8) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j) dma16(src + swz(j * 64 + lane) * 16, dst + j * 1024);
-            if (lane < 2) dma16(src + kF8Exp + lane * 16, dst + kF8Exp);
-        } else {
-#pragma unroll
-            for (int j = 0; j < 8; ++j) dma16(src + swz(j * 64 + lane) * 16, dst + j * 1024);
-        }
+    // Walks the segment's blocks in the order they are issued: sinks, then the
+    // ring.  The table entry of the next block to issue is loaded one issue
+    // ahead.  Every block of a query's visible range holds appended tokens, so
+    // the planner has assigned it.
+    const int ring_blocks = g.ring / kBlock;
+    int vi = v0;
+    int rb = vr.first / kBlock;
+    if (v0 > vr.n_sb) rb = (rb + (v0 - vr.n_sb)) % ring_blocks;
+    auto next_phys = [&]() {
+        const int lb = vi < vr.n_sb ? vi : g.n_sink_blocks + rb;
+        if (vi >= vr.n_sb) rb = rb + 1 == ring_blocks ? 0 : rb + 1;
+        ++vi;
+        return scalar_ld(trow, __builtin_amdgcn_readfirstlane(lb));
     };
-    const int pre = nblk < NBUF - 1 ? nblk : NBUF - 1;
-    for (int i = 0; i < pre; ++i) issue(i);
+    // lane offsets of the copies inside a block: fixed, the base in SGPRs
+    constexpr int NFI = F8 ? 4 : 8;  // 1 KiB instructions
+    uint32_t doff[NFI];
+#pragma unroll
+    for (int j = 0; j < NFI; ++j) doff[j] = (uint32_t)swz(j * 64 + lane) * 16;
+    int ph = nblk > 0 ? next_phys() : 0;  // of the next block to issue
+    auto issue = [&](int i) {
+        const uint8_t *src = head_base + (int64_t)max(ph, 0) * g.block_stride;
+        const uint32_t dst = ring0 + (uint32_t)((i % NBUF) * BLK);
+#pragma unroll
+        for (int j = 0; j < NFI; ++j) dma16_s(doff[j], src, dst + j * 1024);
+        if constexpr (F8) {
+            if (lane < 2) dma16_s(kF8Exp + lane * 16, src, dst + kF8Exp);
+        }
+        if (i + 1 < nblk) ph = next_phys();
+    };
+    for (int i = 0; i < min(nblk, NBUF - 1); ++i) issue(i);
 
     // ---- q prologue: rotate at pos, fold the softmax scale (log2 domain);
     // the B operand of QK MFMA s holds dims 32 g4 + 8 s .. + 7 of head n.
@@ -251,7 +262,9 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
         wave_sync();
     };
 
-    float m_ref = -INFINITY, lsum = 0.f;
+    // the reference starts at the lowest finite float: the first finite score
+    // exceeds it by more than 2^8 and sets it, masked (-inf) scores give 0
+    float m_ref = -3.402823466e38f, lsum = 0.f;
     f32x4_t acc[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -264,17 +277,26 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
     const int vo0 = F8 ? swz(128 + 32 * g4 + 2 * n) * 16 : 0;
     const int vo1 = F8 ? swz(128 + 32 * g4 + 2 * n + 1) * 16 : 0;
 
-    for (int i = 0; i < nblk; ++i) {
-        // block i has landed once at most the blocks issued after it are in flight
-        vm_wait_blocks<NIW, NBUF - 2>(min(NBUF - 2, nblk - 1 - i));
-        if (i + NBUF - 1 < nblk) issue(i + NBUF - 1);
+    // one block; MASKED: it may hold slots that the query cannot see; AHEAD:
+    // see below
+    auto step = [&](int i, auto ahead_c, auto masked_c) __attribute__((always_inline)) {
+        constexpr bool AHEAD = decltype(ahead_c)::value, MASKED = decltype(masked_c)::value;
+        // the slot of block i - 1 takes block i + NBUF - 1; block i has landed
+        // once at most the blocks issued after it are in flight
+        if constexpr (AHEAD) {
+            if (i + NBUF - 1 < nblk) issue(i + NBUF - 1);
+            vm_wait_blocks<NIW, NBUF - 1>(min(NBUF - 1, nblk - 1 - i));
+        } else {
+            vm_wait_blocks<NIW, NBUF - 2>(min(NBUF - 2, nblk - 1 - i));
+            if (i + NBUF - 1 < nblk) issue(i + NBUF - 1);
+        }
         const uint8_t *blk = &ring[wv][i % NBUF][0];
-        int lb, lo, hi;
-        it_proc.get(&lb, &lo, &hi);
-        it_proc.next();
-        if (scalar_ld(trow, __builtin_amdgcn_readfirstlane(lb)) < 0) hi = lo;  // unassigned
-        if (own_new && i == nblk - 1) put_new((uint8_t *)blk);  // slot hi - 1 is the newest key
-        const bool full = lo == 0 && hi == kBlock;
+        int lo = 0, hi = kBlock;
+        if constexpr (MASKED) {
+            int lb;
+            vblock(g, vr, v0 + i, &lb, &lo, &hi);
+            if (own_new && i == nblk - 1) put_new((uint8_t *)blk);  // slot hi - 1 is the newest key
+        }
 
         // QK: S[key][head] for keys 4 g4 + r, head n
         f32x4_t c = {0.f, 0.f, 0.f, 0.f};
@@ -310,7 +332,7 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) sc[r] = c[r];
         }
-        if (!full) {
+        if constexpr (MASKED) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int key = 4 * g4 + r;
@@ -327,17 +349,16 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) acc[j] *= alpha;
         }
-        const float mr = m_ref == -INFINITY ? 0.f : m_ref;
         float pv[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) pv[r] = __builtin_amdgcn_exp2f(sc[r] - mr);
+        for (int r = 0; r < 4; ++r) pv[r] = __builtin_amdgcn_exp2f(sc[r] - m_ref);
         lsum += (pv[0] + pv[1]) + (pv[2] + pv[3]);
         if constexpr (F8) {
             // fold the value scales into the probabilities
 #pragma unroll
             for (int r = 0; r < 4; ++r) pv[r] *= f8_scale(evs, r);
         }
-        if (!full) {
+        if constexpr (MASKED) {
             // invisible slots: zero probability, and zero values (they may be NaN)
             uint32_t bm = 0;
 #pragma unroll
@@ -369,7 +390,31 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
             else
                 acc[j] = mfma_pv(vw2[j], pb, acc[j]);
         }
-    }
+    };
+    // Blocks with invisible slots: the sinks and the window's first block, and
+    // its last one.  Three loops, so that the inner one carries no masks
+    // and no copies of the operands the masked one changes.
+    const int m_a = max(0, min(nblk, vr.n_sb + 1 - v0));
+    const int m_b = max(m_a, v1 == nv ? nblk - 1 : nblk);
+    // A short segment is a chain of memory round trips: its next block is
+    // issued before the wait for the current one.  A long one streams at the
+    // rate of HBM, which a second block in flight per wave lowers.  Per layer,
+    // before against after the wait: 8 fp8 sessions at 8 segments (8 blocks a
+    // wave) 14.7 against 16.3 us, one bf16 session (2 blocks) 11.8 against
+    // 12.5; 128 bf16 sessions (64 blocks) 165.5 against 163.1.  At 16 blocks a
+    // wave the two are nearly alike (256 fp8 sessions, G = 4: 177.2 against
+    // 178.6; 16 bf16 sessions 29.5 against 29.8).  One choice per unit: its
+    // waves, one block apart, would end apart with different ones.
+    auto run = [&](auto ahead_c) __attribute__((always_inline)) {
+        int i = 0;
+        for (; i < m_a; ++i) step(i, ahead_c, std::true_type{});
+        for (; i < m_b; ++i) step(i, ahead_c, std::false_type{});
+        for (; i < nblk; ++i) step(i, ahead_c, std::true_type{});
+    };
+    if (nv <= 20 * (int)nseg)
+        run(std::true_type{});
+    else
+        run(std::false_type{});
 
     float L = rows_sum(lsum);
 
