@@ -222,7 +222,7 @@ mtn_status mtn_frame_append_kv(mtn_pool *pool, int32_t layer, const void *k, con
  * position t is rotated at t and attends to sinks [0, min(S, t+1)) and window
  * [max(S, t-W+1), t] of its own session (all earlier chunk tokens included).
  * lse: device [T][Hq] fp32 natural-log sum-exp of the scaled scores, or NULL.
- * bf16 pools run the MFMA kernel, fp32 pools the fp32 vector kernel.
+ * bf16 and fp8 pools run the bf16 MFMA kernel, fp32 pools an fp32 MFMA kernel.
  */
 mtn_status mtn_attend_chunk_prefill(mtn_pool *pool, int32_t layer, const void *q, void *out,
                                     float *lse, void *stream);

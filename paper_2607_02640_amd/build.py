@@ -22,14 +22,17 @@ COMMON = [
     "-Wall", "-Wno-unused-function", "-Wno-unused-result",
 ]
 
-SOURCES = ["mtn_host.cpp", "mtn_admission.cpp", "mtn_kernels.hip", "mtn_mfma.hip"]
+SOURCES = ["mtn_host.cpp", "mtn_admission.cpp", "mtn_kernels.hip", "mtn_mfma.hip",
+           "mtn_prefill_f32.hip"]
 
 # Per-source code generation.  The matrix-core decode takes its MFMA
 # accumulators in ordinary VGPRs: in the AGPR form the compiler copied the 32
 # output accumulators out of and back into AGPRs around every block's rescale
 # test (about 100 of its 250 vector instructions per block; measured 1.3 %
 # faster fp8 and 0.4 % faster bf16 launches without them).
-EXTRA = {"mtn_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+# The fp32 prefill takes the same form.
+EXTRA = {"mtn_mfma.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+         "mtn_prefill_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 
 
 def compile_flags(src: str) -> list:

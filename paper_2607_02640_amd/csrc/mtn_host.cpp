@@ -395,8 +395,10 @@ void plan_prefill(mtn_pool *P) {
         blocks = std::max(blocks, ceil_div(keys_seen(P, P->seq_pos0[i], P->seq_pos0[i] + P->seq_ntok[i] - 1),
                                            kBlock));
     const int64_t max_split = std::max<int64_t>(1, std::min<int64_t>(blocks / 2 / kPfMinStages, kPfMaxSplit));
-    int64_t rpp = P->pf_rows_cfg ? P->pf_rows_cfg : prefill_rows_per_pass();
-    if (!P->pf_rows_cfg && P->n_cu > 0 && prefill_pass_rows_valid(128) &&
+    const bool f32 = P->cfg.kv_dtype == MTN_F32;  // its kernel has one pass size
+    int64_t rpp = f32 ? prefill_f32_rows_per_pass()
+                      : P->pf_rows_cfg ? P->pf_rows_cfg : prefill_rows_per_pass();
+    if (!f32 && !P->pf_rows_cfg && P->n_cu > 0 && prefill_pass_rows_valid(128) &&
         2 * passes(rpp) <= P->n_cu && passes(128) * max_split <= 2 * (int64_t)P->n_cu)
         rpp = 128;
     P->pf_rows = (int32_t)rpp;
@@ -852,12 +854,12 @@ mtn_status prefill_impl(mtn_pool *P, int32_t layer, const void *q, void *out, fl
     hipEvent_t e0;
     st = timing_begin(P, s, &e0);
     if (st) return st;
-    if (prefill_mfma_supported(P->cfg.kv_dtype, P->cfg.head_dim, P->G)) {
-        HIP_TRY(P, launch_prefill_mfma(P->cfg.kv_dtype, a, P->d_pf_items,
-                                       (int32_t)(P->pf_items.size() / kPfItem), P->pf_rows, P->d_zero, s));
-    } else {
-        HIP_TRY(P, launch_attn_valu(P->cfg.kv_dtype, a, s));
-    }
+    const int32_t n_items = (int32_t)(P->pf_items.size() / kPfItem);
+    if (P->cfg.kv_dtype == MTN_F32)
+        HIP_TRY(P, launch_prefill_f32(a, P->d_pf_items, n_items, s));
+    else
+        HIP_TRY(P, launch_prefill_mfma(P->cfg.kv_dtype, a, P->d_pf_items, n_items, P->pf_rows,
+                                       P->d_zero, s));
     st = timing_end(P, 1, e0, s);
     if (st) return st;
     if (k_new) P->layer_done[layer] = 1;
@@ -1043,7 +1045,8 @@ mtn_status pool_init(mtn_pool *P, const mtn_pool_config *cfg, void *kv_dev, void
     for (auto *v : {&P->tok_sid, &P->tok_pos, &P->tok_row, &P->tok_block, &P->tok_off, &P->upd_idx,
                     &P->upd_val, &P->run_tok0, &P->run_len})
         v->reserve((size_t)P->max_tok);
-    const size_t max_items = (size_t)P->max_tok * P->G / 128 + (size_t)cfg->max_sessions + 1;
+    const size_t max_items = (size_t)P->max_tok * P->G / prefill_f32_rows_per_pass() +
+                             (size_t)cfg->max_sessions + 1;  // the smallest passes'
     P->pf_items.reserve(kPfItem * max_items);
     P->pf_order.reserve(max_items);
     P->layer_done.reserve((size_t)cfg->n_layers);
@@ -1060,12 +1063,8 @@ mtn_status pool_init(mtn_pool *P, const mtn_pool_config *cfg, void *kv_dev, void
                                 (hipStream_t)stream)) != hipSuccess)
             return bail(e, "table upload");
         // per plan: 5 T token fields, 2 U table updates (U <= T), kPfItem per
-        // prefill pass (<= T G / 128 + n_seq passes, aligned to a record) and 2
-        // per append run (<= T)
-        size_t meta = sizeof(int32_t) * ((size_t)P->max_tok * 9 +
-                                         kPfItem * ((size_t)P->max_tok * P->G / 128 +
-                                                    (size_t)cfg->max_sessions + 1) +
-                                         64);
+        // prefill pass (aligned to a record), 2 per append run (<= T)
+        size_t meta = sizeof(int32_t) * ((size_t)P->max_tok * 9 + kPfItem * max_items + 64);
         if ((e = hipMalloc(&P->d_meta, meta)) != hipSuccess) return bail(e, "meta");
         for (int i = 0; i < kStages; ++i) {
             if ((e = hipHostMalloc(&P->h_stage[i], meta, hipHostMallocDefault)) != hipSuccess)

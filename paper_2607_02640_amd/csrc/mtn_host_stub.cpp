@@ -25,6 +25,10 @@ hipError_t launch_prefill_mfma(int, const AttnArgs &, const int32_t *, int32_t, 
                                const uint8_t *, hipStream_t) {
     return hipErrorNotSupported;
 }
+int prefill_f32_rows_per_pass() { return 64; }
+hipError_t launch_prefill_f32(const AttnArgs &, const int32_t *, int32_t, hipStream_t) {
+    return hipErrorNotSupported;
+}
 hipError_t launch_poison(int, const PoolGeom &, int32_t, int64_t, const uint16_t *, hipStream_t) {
     return hipErrorNotSupported;
 }
@@ -55,7 +59,8 @@ int attn_valu_resident_per_cu(int, int, int) { return 1; }
 int attn_valu_groups(int) { return 1; }
 int attn_mfma_groups(int) { return 4; }
 bool prefill_mfma_supported(int dtype, int d, int g) {
-    return ((dtype == 1 && (d == 128 || d == 64)) || (dtype == 2 && d == 128)) && group_ok(g);
+    return (((dtype == 0 || dtype == 1) && (d == 128 || d == 64)) || (dtype == 2 && d == 128)) &&
+           group_ok(g);
 }
 
 }  // namespace mtn

@@ -66,8 +66,8 @@ hipError_t launch_append(int dtype, const PoolGeom &g, const PlanView &p, int32_
                          const void *k, const void *v, const int32_t *run_tok0,
                          const int32_t *run_len, int32_t n_runs, hipStream_t s);
 
-// Vector (VALU) attention over items = planned tokens: decode, and the fp32
-// chunk prefill.  Returns hipErrorInvalidValue for shapes with no instance.
+// Vector (VALU) decode attention over items = planned tokens.  Returns
+// hipErrorInvalidValue for shapes with no instance.
 hipError_t launch_attn_valu(int dtype, const AttnArgs &a, hipStream_t s);
 hipError_t launch_merge(int dtype, const AttnArgs &a, hipStream_t s);
 
@@ -88,6 +88,12 @@ int prefill_rows_per_pass();
 bool prefill_pass_rows_valid(int rows);
 hipError_t launch_prefill_mfma(int dtype, const AttnArgs &a, const int32_t *items, int32_t n_items,
                                int32_t pass_rows, const uint8_t *zero_page, hipStream_t s);
+
+// The same over fp32 pools (D = 64 or 128), a.zero_page the zero page:
+// passes of prefill_f32_rows_per_pass() rows.
+int prefill_f32_rows_per_pass();
+hipError_t launch_prefill_f32(const AttnArgs &a, const int32_t *items, int32_t n_items,
+                              hipStream_t s);
 
 hipError_t launch_poison(int dtype, const PoolGeom &g, int32_t n_layers, int64_t n_blocks,
                          const uint16_t *live_mask, hipStream_t s);

@@ -1,7 +1,7 @@
 // gfx950 (CDNA4) kernels of libmtn: plan upload/apply (block-table updates
-// and fp64 RoPE angles), fused RoPE + append + evict, vector GQA attention
-// over sinks ∪ window (decode, and the fp32 chunk prefill) with a split-K
-// log-sum-exp merge, the debug poison kernel and the HBM copy probe.
+// and fp64 RoPE angles), fused RoPE + append + evict, vector GQA decode
+// attention over sinks ∪ window, the MFMA chunk prefill, the log-sum-exp merge
+// of key segments, the debug poison kernel and the HBM copy probe.
 //
 // Method: Metronome (arXiv 2607.02640) §4.1 / App. A -- a query at absolute
 // position t attends to keys k <= t with k < S or k in the W positions ending
@@ -1689,7 +1689,7 @@ bool attn_valu_supported(int dtype, int d, int g) {
 }
 
 bool prefill_mfma_supported(int dtype, int d, int g) {
-    return ((dtype == 1 && (d == 128 || d == 64)) || (dtype == 2 && d == 128)) && (g == 1 || g == 2 || g == 4 || g == 8);
+    return (((dtype == 0 || dtype == 1) && (d == 128 || d == 64)) || (dtype == 2 && d == 128)) && (g == 1 || g == 2 || g == 4 || g == 8);
 }
 
 hipError_t launch_plan_apply(const int32_t *src, int32_t *dst, int32_t n_words,
@@ -1792,7 +1792,7 @@ void launch_prefill_g(int G, dim3 grid, dim3 block, hipStream_t s, const PfArgs 
 hipError_t launch_prefill_mfma(int dtype, const AttnArgs &a, const int32_t *items, int32_t n_items,
                                int32_t pass_rows, const uint8_t *zero_page, hipStream_t s) {
     const int G = a.g.hq / a.g.hkv;
-    if (!prefill_mfma_supported(dtype, a.g.d, G) || n_items <= 0 || !zero_page || !items ||
+    if (dtype == 0 || !prefill_mfma_supported(dtype, a.g.d, G) || n_items <= 0 || !zero_page || !items ||
         !prefill_pass_rows_valid(pass_rows))
         return hipErrorInvalidValue;
     if (((uintptr_t)items & 31) != 0) return hipErrorInvalidValue;  // records are 32-byte aligned

@@ -30,6 +30,10 @@ def _setup(dtype, hq, hkv, S, W, cmax, n, L=1, d=128):
     ("bf16-d64", 8, 4, 520, 0),  # head dim 64: half the slices, another LDS swizzle
     ("bf16-d64", 2, 20, None, 256),
     ("bf16-d64", 1, 0, 390, 128),
+    ("f32", 8, 4, 390, 0),       # fp32: 64-row passes, several per chunk
+    ("f32", 1, 20, None, 0),
+    ("f32-d64", 4, 17, 400, 0),
+    ("f32-d64", 2, 0, 33, 0),    # chunks longer than the window
 ])
 def test_split_prefill_matches_oracle(dtype, g, S, W, rows):
     """Two sessions of very different lengths in one plan: the short one has
@@ -48,7 +52,7 @@ def test_split_prefill_matches_oracle(dtype, g, S, W, rows):
         pool.kernel_times()
         h.frame([rnd.randint(40, 60), rnd.randint(2, 9)], [1, 0], n_split=1, use_frame_step=f % 3 > 0)
         merges = pool.kernel_times()["merge"][0]
-    assert merges == 1, "the last frames' prefill ran unsplit"
+    assert merges == (W != 33), "the last frame's prefill ran unsplit"
     say(f"max err {h.max_err:.2e}")
 
 

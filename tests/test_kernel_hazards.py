@@ -20,7 +20,7 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2607_02640_amd", "csrc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-SOURCES = ["mtn_kernels.hip", "mtn_mfma.hip"]
+SOURCES = ["mtn_kernels.hip", "mtn_mfma.hip", "mtn_prefill_f32.hip"]
 REG = re.compile(r"\bv(?:\[(\d+):(\d+)\]|(\d+)\b)")
 
 
