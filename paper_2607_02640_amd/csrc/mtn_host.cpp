@@ -132,7 +132,10 @@ struct mtn_pool {
     PlanView view{};
     int32_t *d_pf_items = nullptr;
     int32_t *d_run_tok0 = nullptr, *d_run_len = nullptr;
-    int32_t resident_units = 0;    // decode work units resident on the whole GPU
+    // decode work units that the split rule counts as one round on the whole
+    // GPU: the vector decode's occupancy; for the matrix-core decode the
+    // workgroups holding about 64 KiB of copies in flight per CU
+    int32_t resident_valu = 0, resident_mfma = 0;
     int32_t n_cu = 0;              // compute units of the pool's device
     int32_t pf_rows_cfg = 0;       // chunk-prefill rows per pass: 0 = chosen per plan
     int32_t pf_rows = 0;           // ... of the open plan
@@ -700,30 +703,24 @@ AttnArgs attn_args(mtn_pool *P, int32_t layer, const void *q, void *out, float *
     return a;
 }
 
-// bf16 decode kernel: the MFMA kernel (per-wave LDS rings, all heads of a KV
-// group per block on matrix cores) for D = 128 and G = 8, the vector kernel
-// otherwise.  Measured: at the 128-session G = 8 shape 6.63 TB/s against 5.84
-// for the vector kernel; at the 64-session G = 1 and 256-session G = 4 shapes
-// the vector kernel's one-wave workgroups win (6.86 and 6.68 TB/s against
-// 6.61 and 6.53).
+// Decode kernel of a launch of `units` (query, kv head) pairs: whether it is the
+// MFMA kernel (per-wave LDS rings, all heads of a KV group per block on matrix
+// cores), which every FP8 pool takes, or the vector kernel (fp32, head dim 64).
+// bf16 at head dim 128 takes the MFMA kernel at G = 8, and at smaller groups up
+// to two units per CU: there its eight waves per unit need no or fewer segments
+// (per layer with the merge, G = 4: 32 units 14.6 us against 17.2, 240 units
+// 42.7 against 49.2, 480 units 83.5 against 85.9; G = 1: 256 units 45.3 against
+// 48.3).  Beyond, the vector kernel's one-wave workgroups stream better (G = 4:
+// 960 units 156 us against 166, 2048 units 334 against 357; G = 1: 2048 units
+// 332 against 350).  At G = 8 the MFMA kernel wins throughout (512 units 6.63
+// TB/s against 5.84).
 // mtn_pool_set_decode_kernel can force either kernel where it exists.
-bool use_mfma_bf16(const mtn_pool *P) {
+bool use_mfma(const mtn_pool *P, int64_t units) {
+    if (P->cfg.kv_dtype == MTN_FP8_E4M3) return true;
     if (P->cfg.kv_dtype != MTN_BF16 || !attn_mfma_bf16_supported(P->cfg.head_dim, P->G))
         return false;
-    if (P->decode_kernel == 1) return false;
-    if (P->decode_kernel == 2) return true;
-    return P->G == 8;
-}
-
-// decode work units the split rule counts as one round on the whole GPU: the
-// kernels' own per-CU figure (the vector decode's occupancy; for the
-// matrix-core decode the workgroups holding about 64 KiB of copies in flight)
-int32_t count_resident_units(const mtn_pool *P) {
-    const mtn_pool_config &c = P->cfg;
-    const int per_cu = c.kv_dtype == MTN_FP8_E4M3 ? attn_fp8_resident_per_cu(P->G)
-                       : use_mfma_bf16(P)         ? attn_mfma_bf16_resident_per_cu(P->G)
-                                                  : attn_valu_resident_per_cu(c.kv_dtype, c.head_dim, P->G);
-    return P->n_cu * per_cu;
+    if (P->decode_kernel) return P->decode_kernel == 2;
+    return P->G == 8 || units <= 2 * (int64_t)P->n_cu;
 }
 
 // Decode split heuristic.  A unit (query, kv head, segment) streams its keys
@@ -747,9 +744,9 @@ int32_t count_resident_units(const mtn_pool *P) {
 int32_t auto_split(const mtn_pool *P, int32_t n_items) {
     const int64_t units = std::max<int64_t>((int64_t)n_items * P->cfg.n_kv_heads, 1);
     const int64_t max_keys = P->unbounded ? P->cfg.max_len : (int64_t)P->S + P->W;
-    const int64_t resident = std::max<int32_t>(P->resident_units, 1);
+    const bool mfma = use_mfma(P, units);
+    const int64_t resident = std::max<int32_t>(mfma ? P->resident_mfma : P->resident_valu, 1);
     if (units >= resident) return 1;
-    const bool mfma = P->cfg.kv_dtype == MTN_FP8_E4M3 || use_mfma_bf16(P);
     const int64_t groups = mfma ? attn_mfma_groups(P->G) : attn_valu_groups(P->G);
     const int64_t blocks = (ceil_div(max_keys, kBlock) + 1) / groups;  // of a wave group, unsplit
     const int64_t fine = std::min<int64_t>(blocks / 2, P->n_cu / units);
@@ -796,7 +793,7 @@ mtn_status decode_impl(mtn_pool *P, int32_t layer, const void *q, void *out, flo
     }
     if (P->cfg.kv_dtype == MTN_FP8_E4M3)
         HIP_TRY(P, launch_attn_fp8(a, s));
-    else if (use_mfma_bf16(P))
+    else if (use_mfma(P, (int64_t)P->T * P->cfg.n_kv_heads))
         HIP_TRY(P, launch_attn_mfma_bf16(a, s));
     else
         HIP_TRY(P, launch_attn_valu(P->cfg.kv_dtype, a, s));
@@ -1111,7 +1108,13 @@ mtn_status pool_init(mtn_pool *P, const mtn_pool_config *cfg, void *kv_dev, void
             return bail(e, "partials");
         if ((e = scratch_buffer(&P->d_scratch, &P->scratch_floats)) != hipSuccess)
             return bail(e, "static scratch address");
-        P->resident_units = count_resident_units(P);
+        const bool fp8 = cfg->kv_dtype == MTN_FP8_E4M3;
+        if (fp8)
+            P->resident_mfma = n_cu * attn_fp8_resident_per_cu(P->G);
+        else if (cfg->kv_dtype == MTN_BF16 && attn_mfma_bf16_supported(cfg->head_dim, P->G))
+            P->resident_mfma = n_cu * attn_mfma_bf16_resident_per_cu(P->G);
+        if (!fp8)
+            P->resident_valu = n_cu * attn_valu_resident_per_cu(cfg->kv_dtype, cfg->head_dim, P->G);
         if ((e = hipEventCreateWithFlags(&P->order_ev, hipEventDisableTiming)) != hipSuccess)
             return bail(e, "event");
         if ((e = hipStreamSynchronize((hipStream_t)stream)) != hipSuccess)
@@ -1468,7 +1471,6 @@ mtn_status mtn_pool_set_decode_kernel(mtn_pool *P, int32_t kind) {
         if (kind == 2 && !attn_mfma_bf16_supported(c.head_dim, P->G))
             return fail(P, MTN_ERR_UNSUPPORTED, "no matrix decode kernel for this shape");
         P->decode_kernel = kind;
-        if (!P->host_only) P->resident_units = count_resident_units(P);
         return MTN_OK;
     });
 }
