@@ -133,8 +133,11 @@ struct mtn_pool {
     int32_t *d_pf_items = nullptr;
     int32_t *d_run_tok0 = nullptr, *d_run_len = nullptr;
     // decode work units that the split rule counts as one round on the whole
-    // GPU: the vector decode's occupancy; for the matrix-core decode the
-    // workgroups holding about 64 KiB of copies in flight per CU
+    // GPU: the vector decode's occupancy, at most 4 per CU (more one-wave
+    // workgroups in flight do not stream faster: at 8 or 16 per CU the rule
+    // halved units for 168 us against 156 with 960 units of G = 4, D = 128, and
+    // for 177 against 167 with 2048 of D = 64); for the matrix-core decode
+    // the workgroups holding about 64 KiB of copies in flight per CU
     int32_t resident_valu = 0, resident_mfma = 0;
     int32_t n_cu = 0;              // compute units of the pool's device
     int32_t pf_rows_cfg = 0;       // chunk-prefill rows per pass: 0 = chosen per plan
@@ -705,22 +708,26 @@ AttnArgs attn_args(mtn_pool *P, int32_t layer, const void *q, void *out, float *
 
 // Decode kernel of a launch of `units` (query, kv head) pairs: whether it is the
 // MFMA kernel (per-wave LDS rings, all heads of a KV group per block on matrix
-// cores), which every FP8 pool takes, or the vector kernel (fp32, head dim 64).
-// bf16 at head dim 128 takes the MFMA kernel at G = 8, and at smaller groups up
-// to two units per CU: there its eight waves per unit need no or fewer segments
+// cores), which every FP8 pool takes, or the vector kernel, which every fp32 pool
+// takes.  bf16 takes the MFMA kernel at G = 8, and at smaller groups up to two
+// units per CU (head dim 64: four), where its eight waves per unit need no or
+// fewer segments
 // (per layer with the merge, G = 4: 32 units 14.6 us against 17.2, 240 units
 // 42.7 against 49.2, 480 units 83.5 against 85.9; G = 1: 256 units 45.3 against
 // 48.3).  Beyond, the vector kernel's one-wave workgroups stream better (G = 4:
 // 960 units 156 us against 166, 2048 units 334 against 357; G = 1: 2048 units
 // 332 against 350).  At G = 8 the MFMA kernel wins throughout (512 units 6.63
-// TB/s against 5.84).
+// TB/s against 5.84).  Head dim 64: G = 8, 42 units 10.5 us against 14.6, 512
+// units 85.4 against 108.1, 1024 units 165.8 against 199.6; G = 4, 480 units
+// 42.5 against 48.8, 960 units 82.1 against 86.8, 2048 units 175 against 167;
+// G = 1, 960 units 81.6 against 84.1, 2048 units 172 against 162.
 // mtn_pool_set_decode_kernel can force either kernel where it exists.
 bool use_mfma(const mtn_pool *P, int64_t units) {
     if (P->cfg.kv_dtype == MTN_FP8_E4M3) return true;
     if (P->cfg.kv_dtype != MTN_BF16 || !attn_mfma_bf16_supported(P->cfg.head_dim, P->G))
         return false;
     if (P->decode_kernel) return P->decode_kernel == 2;
-    return P->G == 8 || units <= 2 * (int64_t)P->n_cu;
+    return P->G == 8 || units <= (P->cfg.head_dim == 64 ? 4 : 2) * (int64_t)P->n_cu;
 }
 
 // Decode split heuristic.  A unit (query, kv head, segment) streams its keys
@@ -1112,9 +1119,10 @@ mtn_status pool_init(mtn_pool *P, const mtn_pool_config *cfg, void *kv_dev, void
         if (fp8)
             P->resident_mfma = n_cu * attn_fp8_resident_per_cu(P->G);
         else if (cfg->kv_dtype == MTN_BF16 && attn_mfma_bf16_supported(cfg->head_dim, P->G))
-            P->resident_mfma = n_cu * attn_mfma_bf16_resident_per_cu(P->G);
+            P->resident_mfma = n_cu * attn_mfma_bf16_resident_per_cu(cfg->head_dim, P->G);
         if (!fp8)
-            P->resident_valu = n_cu * attn_valu_resident_per_cu(cfg->kv_dtype, cfg->head_dim, P->G);
+            P->resident_valu =
+                n_cu * std::min(4, attn_valu_resident_per_cu(cfg->kv_dtype, cfg->head_dim, P->G));
         if ((e = hipEventCreateWithFlags(&P->order_ev, hipEventDisableTiming)) != hipSuccess)
             return bail(e, "event");
         if ((e = hipStreamSynchronize((hipStream_t)stream)) != hipSuccess)
@@ -1468,7 +1476,7 @@ mtn_status mtn_pool_set_decode_kernel(mtn_pool *P, int32_t kind) {
             return fail(P, MTN_ERR_UNSUPPORTED, "the FP8 cache has no vector decode kernel");
         if (kind == 2 && c.kv_dtype == MTN_F32)
             return fail(P, MTN_ERR_UNSUPPORTED, "fp32 pools have no matrix decode kernel");
-        if (kind == 2 && !attn_mfma_bf16_supported(c.head_dim, P->G))
+        if (kind == 2 && (c.head_dim != 128 || !attn_mfma_bf16_supported(c.head_dim, P->G)))
             return fail(P, MTN_ERR_UNSUPPORTED, "no matrix decode kernel for this shape");
         P->decode_kernel = kind;
         return MTN_OK;

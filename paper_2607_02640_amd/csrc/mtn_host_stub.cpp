@@ -49,8 +49,8 @@ hipError_t launch_attn_fp8(const AttnArgs &, hipStream_t) { return hipErrorNotSu
 hipError_t launch_poison_fp8(const PoolGeom &, int32_t, int64_t, const uint16_t *, hipStream_t) {
     return hipErrorNotSupported;
 }
-bool attn_mfma_bf16_supported(int d, int g) { return attn_fp8_supported(d, g); }
-int attn_mfma_bf16_resident_per_cu(int) { return 1; }
+bool attn_mfma_bf16_supported(int d, int g) { return (d == 128 || d == 64) && group_ok(g); }
+int attn_mfma_bf16_resident_per_cu(int, int) { return 1; }
 hipError_t launch_attn_mfma_bf16(const AttnArgs &, hipStream_t) { return hipErrorNotSupported; }
 bool attn_valu_supported(int dtype, int d, int g) {
     return (dtype == 0 || dtype == 1) && (d == 64 || d == 128) && group_ok(g);

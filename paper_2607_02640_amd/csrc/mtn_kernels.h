@@ -121,9 +121,9 @@ hipError_t launch_attn_fp8(const AttnArgs &a, hipStream_t s);
 hipError_t launch_poison_fp8(const PoolGeom &g, int32_t n_layers, int64_t n_blocks,
                              const uint16_t *live_mask, hipStream_t s);
 
-// The same MFMA decode over bf16 blocks (D = 128, bf16 io), append fusable.
+// The same MFMA decode over bf16 blocks (D = 128 or 64, bf16 io), append fusable.
 bool attn_mfma_bf16_supported(int d, int g);
-int attn_mfma_bf16_resident_per_cu(int g);
+int attn_mfma_bf16_resident_per_cu(int d, int g);
 hipError_t launch_attn_mfma_bf16(const AttnArgs &a, hipStream_t s);
 
 bool attn_valu_supported(int dtype, int d, int g);

@@ -73,20 +73,21 @@ __global__ __launch_bounds__(256) void k_append_fp8(PoolGeom g, PlanView p, int3
 }
 
 // ---------------------------------------------------------------------------
-// MFMA decode attention over fp8 blocks (F8) or bf16 blocks, D = 128
+// MFMA decode attention over fp8 blocks (F8, D = 128) or bf16 blocks (D = 128
+// or 64)
 // ---------------------------------------------------------------------------
 // One work unit = (query token, kv head, split segment), one workgroup of NG
 // waves; the unit's keys are cut into NG consecutive segments and each wave
 // streams its own segment through its own LDS ring of NBUF blocks (no
 // barrier inside the loop).  Per block, one wave computes all G heads:
-//   S[key][head]  = K[key][:] . Q^T   four 16x16x32 MFMAs (A = K as bf16)
-//   O^T[d][head] += V^T[d][key] . P'  eight 16x16x16 MFMAs (A = V as bf16)
+//   S[key][head]  = K[key][:] . Q^T   D / 32 16x16x32 MFMAs (A = K as bf16)
+//   O^T[d][head] += V^T[d][key] . P'  D / 16 16x16x16 MFMAs (A = V as bf16)
 // (fp8 codes convert to bf16 exactly; bf16 blocks are used as they are).
 // Lane l (n = l % 16, g4 = l / 16) holds head n (heads >= G are zero
-// queries): its QK B operand covers dims 32 g4 .. 32 g4 + 31, its scores are
+// queries): its QK B operand covers dims D/4 g4 .. + D/4 - 1, its scores are
 // keys 4 g4 .. 4 g4 + 3, which is exactly its PV B operand, and its output
-// accumulators are dims 32 g4 + 8 i + j (i < 4, j < 8) -- the PV MFMA j
-// takes dims 8 m + j on its rows m.  The online softmax keeps a per-head
+// accumulators are dims D/4 g4 + D/16 i + j (i < 4, j < D/16) -- the PV MFMA j
+// takes dims D/16 m + j on its rows m.  The online softmax keeps a per-head
 // reference max that moves only when a block's max exceeds it by more than
 // 2^8, so the accumulator rescale is rare.  At the end the waves' (max, sum,
 // acc) are merged through LDS by log-sum-exp.
@@ -109,13 +110,16 @@ struct MfmaShape {
 #endif
 };
 
-template <bool F8, int G, int NG, int NBUF>
+template <int D, bool F8, int G, int NG, int NBUF>
 __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
-    constexpr int D = kF8D;
+    static_assert(D == kF8D || (D == 64 && !F8), "head dims with a block layout");
+    constexpr int ND = D / 32;   // QK MFMAs per block
+    constexpr int NJ = D / 16;   // PV MFMAs per block
+    constexpr int VD = D / 64;   // dims per lane of a row
     // one block's ring slot: fp8 codes + exponents, or the bf16 K and V^T tiles
     constexpr int BLK = F8 ? kF8Read : 2 * kBlock * D * 2;
-    // DMA instructions per block: 4 x 1 KiB + the 32 exponent bytes, or 8 x 1 KiB
-    constexpr int NIW = F8 ? 5 : 8;
+    // DMA instructions per block: 4 x 1 KiB + the 32 exponent bytes, or 1 KiB each
+    constexpr int NIW = F8 ? 5 : BLK / 1024;
     static_assert(G >= 1 && G <= 16, "heads per kv group");
     static_assert(NBUF >= 2 && NBUF <= 8, "ring depth");
     static_assert(NBUF * BLK >= 16 * D * 4, "merge scratch fits one wave's ring");
@@ -163,7 +167,7 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
         return scalar_ld(trow, __builtin_amdgcn_readfirstlane(lb));
     };
     // lane offsets of the copies inside a block: fixed, the base in SGPRs
-    constexpr int NFI = F8 ? 4 : 8;  // 1 KiB instructions
+    constexpr int NFI = F8 ? 4 : NIW;  // 1 KiB instructions
     uint32_t doff[NFI];
 #pragma unroll
     for (int j = 0; j < NFI; ++j) doff[j] = (uint32_t)swz(j * 64 + lane) * 16;
@@ -181,17 +185,17 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
     for (int i = 0; i < min(nblk, NBUF - 1); ++i) issue(i);
 
     // ---- q prologue: rotate at pos, fold the softmax scale (log2 domain);
-    // the B operand of QK MFMA s holds dims 32 g4 + 8 s .. + 7 of head n.
-    const int d0 = 32 * g4;
-    const int dp = d0 ^ 64;  // RoPE partner dims
-    uint4 qb[4];
-    const float2 *rp = a.p.rope + (int64_t)t * (D / 2) + (d0 & 63);
+    // the B operand of QK MFMA s holds dims D/4 g4 + 8 s .. + 7 of head n.
+    const int d0 = D / 4 * g4;
+    const int dp = d0 ^ (D / 2);  // RoPE partner dims
+    uint4 qb[ND];
+    const float2 *rp = a.p.rope + (int64_t)t * (D / 2) + (d0 & (D / 2 - 1));
     const float sgn = g4 < 2 ? -1.f : 1.f;
     {
         const bool hv = n < G;
         const bf16_t *qh = (const bf16_t *)a.q + (row * g.hq + (int64_t)kvh * G + (hv ? n : 0)) * D;
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
+        for (int s = 0; s < ND; ++s) {
             float x[8], y[8];
             unpack8(((const uint4 *)(qh + d0))[s], x);
             unpack8(((const uint4 *)(qh + dp))[s], y);
@@ -206,37 +210,42 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
             qb[s] = make_uint4(w[0], w[1], w[2], w[3]);
         }
     }
-    // The owner rotates (and, fp8, quantizes) the newest key and value two
-    // dims per lane (dims d0 + 2 n, d0 + 2 n + 1), exactly as the append
-    // kernel does.
-    uint32_t kc2 = 0, vc2 = 0;
+    // The owner rotates (and, fp8, quantizes) the newest key and value, VD dims
+    // per lane (dims d0 + VD n ..), exactly as the append kernel does.
+    uint32_t kc2 = 0, vc2 = 0;  // the lane's stored elements, the first in the low bits
     int ek_new = 0, ev_new = 0;
-    const int dd = d0 + 2 * n;
+    const int dd = d0 + VD * n;
     if (own_new) {
         const bf16_t *kh = (const bf16_t *)a.k_new + (row * g.hkv + kvh) * D;
         const bf16_t *vh = (const bf16_t *)a.v_new + (row * g.hkv + kvh) * D;
-        const uint32_t kx = *(const uint32_t *)(kh + dd), ky = *(const uint32_t *)(kh + (dd ^ 64));
-        const uint32_t vx = *(const uint32_t *)(vh + dd);
-        const float4 cs = *(const float4 *)(rp + 2 * n);  // (cos, sin) of dims dd, dd + 1
-        // rotated exactly as the append kernel does
-        const float k0 = fmaf(__uint_as_float(kx << 16), cs.x, sgn * __uint_as_float(ky << 16) * cs.y);
-        const float k1 = fmaf(__uint_as_float(kx & 0xFFFF0000u), cs.z,
-                              sgn * __uint_as_float(ky & 0xFFFF0000u) * cs.w);
-        if constexpr (F8) {
-            const float v0 = __uint_as_float(vx << 16), v1 = __uint_as_float(vx & 0xFFFF0000u);
-            float ak = fmaxf(fabsf(k0), fabsf(k1)), av = fmaxf(fabsf(v0), fabsf(v1));
-#pragma unroll
-            for (int m = 1; m < 16; m <<= 1) {  // the 16 lanes of a row, then the rows
-                ak = fmaxf(ak, __shfl_xor(ak, m, 64));
-                av = fmaxf(av, __shfl_xor(av, m, 64));
-            }
-            ek_new = __builtin_amdgcn_readfirstlane(f8_scale_exp(rows_max(ak)));
-            ev_new = __builtin_amdgcn_readfirstlane(f8_scale_exp(rows_max(av)));
-            kc2 = f8_pack<false>(ldexpf(k0, -ek_new), ldexpf(k1, -ek_new), 0u);
-            vc2 = f8_pack<false>(ldexpf(v0, -ev_new), ldexpf(v1, -ev_new), 0u);
+        if constexpr (VD == 1) {
+            const float2 cs = rp[n];
+            const float k0 = fmaf(to_f32(kh[dd]), cs.x, sgn * to_f32(kh[dd ^ (D / 2)]) * cs.y);
+            kc2 = from_f32<bf16_t>(k0).bits;  // rounded to the stored type as the append does
+            vc2 = vh[dd].bits;
         } else {
-            kc2 = pack_bf16x2(k0, k1);  // rounded to the stored type as the append does
-            vc2 = vx;
+            const uint32_t kx = *(const uint32_t *)(kh + dd), ky = *(const uint32_t *)(kh + (dd ^ 64));
+            const uint32_t vx = *(const uint32_t *)(vh + dd);
+            const float4 cs = *(const float4 *)(rp + 2 * n);  // (cos, sin) of dims dd, dd + 1
+            const float k0 = fmaf(__uint_as_float(kx << 16), cs.x, sgn * __uint_as_float(ky << 16) * cs.y);
+            const float k1 = fmaf(__uint_as_float(kx & 0xFFFF0000u), cs.z,
+                                  sgn * __uint_as_float(ky & 0xFFFF0000u) * cs.w);
+            if constexpr (F8) {
+                const float v0 = __uint_as_float(vx << 16), v1 = __uint_as_float(vx & 0xFFFF0000u);
+                float ak = fmaxf(fabsf(k0), fabsf(k1)), av = fmaxf(fabsf(v0), fabsf(v1));
+#pragma unroll
+                for (int m = 1; m < 16; m <<= 1) {  // the 16 lanes of a row, then the rows
+                    ak = fmaxf(ak, __shfl_xor(ak, m, 64));
+                    av = fmaxf(av, __shfl_xor(av, m, 64));
+                }
+                ek_new = __builtin_amdgcn_readfirstlane(f8_scale_exp(rows_max(ak)));
+                ev_new = __builtin_amdgcn_readfirstlane(f8_scale_exp(rows_max(av)));
+                kc2 = f8_pack<false>(ldexpf(k0, -ek_new), ldexpf(k1, -ek_new), 0u);
+                vc2 = f8_pack<false>(ldexpf(v0, -ev_new), ldexpf(v1, -ev_new), 0u);
+            } else {
+                kc2 = pack_bf16x2(k0, k1);
+                vc2 = vx;
+            }
         }
     }
     const int toff = __builtin_amdgcn_readfirstlane(a.p.tok_off[t]);  // the newest key's slot
@@ -254,10 +263,14 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
                 blk[kF8Exp + kBlock + toff] = (uint8_t)(ev_new + 127);
             }
         } else {
-            *(uint32_t *)at((toff * D + dd) * 2) = kc2;
             const int vb = kBlock * D * 2 + (dd * kBlock + toff) * 2;  // V^T [D][16]
             *(uint16_t *)at(vb) = (uint16_t)vc2;
-            *(uint16_t *)at(vb + kBlock * 2) = (uint16_t)(vc2 >> 16);
+            if constexpr (VD == 2) {
+                *(uint32_t *)at((toff * D + dd) * 2) = kc2;
+                *(uint16_t *)at(vb + kBlock * 2) = (uint16_t)(vc2 >> 16);
+            } else {
+                *(uint16_t *)at((toff * D + dd) * 2) = (uint16_t)kc2;
+            }
         }
         wave_sync();
     };
@@ -265,14 +278,14 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
     // the reference starts at the lowest finite float: the first finite score
     // exceeds it by more than 2^8 and sets it, masked (-inf) scores give 0
     float m_ref = -3.402823466e38f, lsum = 0.f;
-    f32x4_t acc[8];
+    f32x4_t acc[NJ];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NJ; ++j) acc[j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     // per-lane LDS offsets of the K and V fragments inside a ring slot (the
     // chunk swizzle keeps each 16-lane read phase on 16 distinct bank groups)
     //   fp8:  K chunks 8 n + 2 g4 (+1); V quads chunks 128 + 32 g4 + 2 n (+1)
-    //   bf16: K chunks 16 n + 4 g4 + s; V^T row 8 n + j, keys 4 g4 .. + 3 at
-    //         chunk 256 + 2 (8 n + j) + g4 / 2, byte 8 (g4 % 2)
+    //   bf16: K chunks NJ / 2 (4 n + g4) + s; V^T row NJ n + j, keys 4 g4 .. + 3 at
+    //         chunk 2 D + 2 (NJ n + j) + g4 / 2, byte 8 (g4 % 2)
     const int ko0 = F8 ? swz(8 * n + 2 * g4) * 16 : 0, ko1 = F8 ? swz(8 * n + 2 * g4 + 1) * 16 : 0;
     const int vo0 = F8 ? swz(128 + 32 * g4 + 2 * n) * 16 : 0;
     const int vo1 = F8 ? swz(128 + 32 * g4 + 2 * n + 1) * 16 : 0;
@@ -300,8 +313,8 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
 
         // QK: S[key][head] for keys 4 g4 + r, head n
         f32x4_t c = {0.f, 0.f, 0.f, 0.f};
-        uint2 vw2[8];  // PV A operands (4 keys of dim 8 n + j), bf16 pool
-        uint32_t vw[8];  // the same as fp8 codes
+        uint2 vw2[NJ];  // PV A operands (4 keys of dim NJ n + j), bf16 pool
+        uint32_t vw[NJ];  // the same as fp8 codes
         uint32_t evs = 0;
         float sc[4];
         if constexpr (F8) {
@@ -324,11 +337,11 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
             for (int r = 0; r < 4; ++r) sc[r] = c[r] * f8_scale(eks, r);
         } else {
 #pragma unroll
-            for (int s = 0; s < 4; ++s)
-                c = mfma16x16x32(*(const uint4 *)(blk + swz(16 * n + 4 * g4 + s) * 16), qb[s], c);
+            for (int s = 0; s < ND; ++s)
+                c = mfma16x16x32(*(const uint4 *)(blk + swz(NJ / 2 * (4 * n + g4) + s) * 16), qb[s], c);
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
-                vw2[j] = *(const uint2 *)(blk + swz(256 + 16 * n + 2 * j + (g4 >> 1)) * 16 + 8 * (g4 & 1));
+            for (int j = 0; j < NJ; ++j)
+                vw2[j] = *(const uint2 *)(blk + swz(2 * D + 2 * (NJ * n + j) + (g4 >> 1)) * 16 + 8 * (g4 & 1));
 #pragma unroll
             for (int r = 0; r < 4; ++r) sc[r] = c[r];
         }
@@ -347,7 +360,7 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
             m_ref = mnew;
             lsum *= alpha;
 #pragma unroll
-            for (int j = 0; j < 8; ++j) acc[j] *= alpha;
+            for (int j = 0; j < NJ; ++j) acc[j] *= alpha;
         }
         float pv[4];
 #pragma unroll
@@ -370,13 +383,13 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
             }
             if constexpr (F8) {
 #pragma unroll
-                for (int j = 0; j < 8; ++j) vw[j] &= bm;
+                for (int j = 0; j < NJ; ++j) vw[j] &= bm;
             } else {
                 // bf16 keys: two bytes of the mask per key
                 const uint32_t m01 = (bm & 0x1u ? 0x0000FFFFu : 0u) | (bm & 0x100u ? 0xFFFF0000u : 0u);
                 const uint32_t m23 = (bm & 0x10000u ? 0x0000FFFFu : 0u) | (bm & 0x1000000u ? 0xFFFF0000u : 0u);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) {
+                for (int j = 0; j < NJ; ++j) {
                     vw2[j].x &= m01;
                     vw2[j].y &= m23;
                 }
@@ -384,7 +397,7 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
         }
         const uint2 pb = make_uint2(pack_bf16x2(pv[0], pv[1]), pack_bf16x2(pv[2], pv[3]));
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 0; j < NJ; ++j) {
             if constexpr (F8)
                 acc[j] = mfma_pv(make_uint2(f8_bf16x2<false>(vw[j]), f8_bf16x2<true>(vw[j])), pb, acc[j]);
             else
@@ -435,90 +448,72 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
                 tile[kF8Exp + kBlock + toff] = (uint8_t)(ev_new + 127);
             }
         } else {
-            *(uint32_t *)(tile + (toff * D + dd) * 2) = kc2;  // K row elements dd, dd + 1
             uint16_t *vt = (uint16_t *)(tile + g.tile_bytes);  // V^T [D][16]
             vt[dd * kBlock + toff] = (uint16_t)vc2;
-            vt[(dd + 1) * kBlock + toff] = (uint16_t)(vc2 >> 16);
+            if constexpr (VD == 2) {
+                *(uint32_t *)(tile + (toff * D + dd) * 2) = kc2;  // K row elements dd, dd + 1
+                vt[(dd + 1) * kBlock + toff] = (uint16_t)(vc2 >> 16);
+            } else {
+                *(uint16_t *)(tile + (toff * D + dd) * 2) = (uint16_t)kc2;
+            }
         }
     };
 
     const int hq0 = kvh * G;
-    if constexpr (NG > 1) {
-        // every wave hands (m, l, acc) over through its own drained ring; then
-        // all threads of the workgroup merge them by log-sum-exp, one pair of
-        // output dims per thread and step (a wave covers one head's row)
-        float *scr = (float *)&ring[wv][0][0] + n * D + d0;  // [16][D]
+    // every wave hands (m, l, acc) over through its own drained ring; then all
+    // threads of the workgroup merge them by log-sum-exp, VD output dims per
+    // thread and step (a wave covers one head's row)
+    static_assert(NG > 1, "the waves merge through LDS");
+    float *scr = (float *)&ring[wv][0][0] + n * D + d0;  // [16][D]
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            *(float4 *)(scr + 8 * i) = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
-            *(float4 *)(scr + 8 * i + 4) = make_float4(acc[4][i], acc[5][i], acc[6][i], acc[7][i]);
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; j += 4)
+            *(float4 *)(scr + NJ * i + j) = make_float4(acc[j][i], acc[j + 1][i], acc[j + 2][i], acc[j + 3][i]);
+    if (g4 == 0) {
+        sM[wv][n] = m_ref;
+        sL[wv][n] = L;
+    }
+    __syncthreads();
+    if (own_new) store_new();
+    for (int e = threadIdx.x; e < G * 64; e += 64 * NG) {
+        const int h = e >> 6, d = VD * (e & 63);
+        float M = sM[0][h];
+#pragma unroll
+        for (int q = 1; q < NG; ++q) M = fmaxf(M, sM[q][h]);
+        float l = 0.f, o[VD];
+#pragma unroll
+        for (int r = 0; r < VD; ++r) o[r] = 0.f;
+#pragma unroll
+        for (int q = 0; q < NG; ++q) {
+            const float wq = __builtin_amdgcn_exp2f(sM[q][h] - M);
+            const float *x = (const float *)&ring[q][0][0] + h * D + d;
+            l = fmaf(sL[q][h], wq, l);
+#pragma unroll
+            for (int r = 0; r < VD; ++r) o[r] = fmaf(wq, x[r], o[r]);
         }
-        if (g4 == 0) {
-            sM[wv][n] = m_ref;
-            sL[wv][n] = L;
-        }
-        __syncthreads();
-        if (own_new) store_new();
-        for (int e = threadIdx.x; e < G * (D / 2); e += 64 * NG) {
-            const int h = e / (D / 2), d = 2 * (e % (D / 2));
-            float M = sM[0][h];
-#pragma unroll
-            for (int q = 1; q < NG; ++q) M = fmaxf(M, sM[q][h]);
-            const float Mn = M == -INFINITY ? 0.f : M;
-            float l = 0.f, o0 = 0.f, o1 = 0.f;
-#pragma unroll
-            for (int q = 0; q < NG; ++q) {
-                const float wq = __builtin_amdgcn_exp2f(sM[q][h] - Mn);
-                const float2 x = *(const float2 *)((const float *)&ring[q][0][0] + h * D + d);
-                l = fmaf(sL[q][h], wq, l);
-                o0 = fmaf(wq, x.x, o0);
-                o1 = fmaf(wq, x.y, o1);
-            }
-            if (a.n_split == 1) {
-                const float inv = 1.f / l;
-                *(uint32_t *)((bf16_t *)a.out + (row * g.hq + hq0 + h) * D + d) = pack_bf16x2(o0 * inv, o1 * inv);
-                if (a.lse && d == 0)
-                    a.lse[row * g.hq + hq0 + h] = (M + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
-            } else {
-                const int64_t base = ((int64_t)t * g.hq + hq0 + h) * ns + split;
-                *(float2 *)(a.part + base * D + d) = make_float2(o0, o1);
-                if (d == 0) {
-                    float *pml = a.part + (int64_t)a.p.n_tok * g.hq * ns * D;
-                    pml[base * 2] = M;
-                    pml[base * 2 + 1] = l;
-                }
-            }
-        }
-    } else {
-        if (n < G) {
-            if (a.n_split == 1) {
-                const float inv = 1.f / L;
-                bf16_t *ob = (bf16_t *)a.out + (row * g.hq + hq0 + n) * D + d0;
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    *(uint4 *)(ob + 8 * i) =
-                        make_uint4(pack_bf16x2(acc[0][i] * inv, acc[1][i] * inv),
-                                   pack_bf16x2(acc[2][i] * inv, acc[3][i] * inv),
-                                   pack_bf16x2(acc[4][i] * inv, acc[5][i] * inv),
-                                   pack_bf16x2(acc[6][i] * inv, acc[7][i] * inv));
-                if (a.lse && g4 == 0)
-                    a.lse[row * g.hq + hq0 + n] = (m_ref + __builtin_amdgcn_logf(L)) * 0.6931471805599453f;
-            } else {
-                const int64_t base = ((int64_t)t * g.hq + hq0 + n) * ns + split;
-                float *pacc = a.part + base * D + d0;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    *(float4 *)(pacc + 8 * i) = make_float4(acc[0][i], acc[1][i], acc[2][i], acc[3][i]);
-                    *(float4 *)(pacc + 8 * i + 4) = make_float4(acc[4][i], acc[5][i], acc[6][i], acc[7][i]);
-                }
-                if (g4 == 0) {
-                    float *pml = a.part + (int64_t)a.p.n_tok * g.hq * ns * D;
-                    pml[base * 2] = m_ref;
-                    pml[base * 2 + 1] = L;
-                }
+        if (a.n_split == 1) {
+            const float inv = 1.f / l;
+            bf16_t *ob = (bf16_t *)a.out + (row * g.hq + hq0 + h) * D + d;
+            if constexpr (VD == 2)
+                *(uint32_t *)ob = pack_bf16x2(o[0] * inv, o[1] * inv);
+            else
+                *ob = from_f32<bf16_t>(o[0] * inv);
+            if (a.lse && d == 0)
+                a.lse[row * g.hq + hq0 + h] = (M + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+        } else {
+            const int64_t base = ((int64_t)t * g.hq + hq0 + h) * ns + split;
+            float *po = a.part + base * D + d;
+            if constexpr (VD == 2)
+                *(float2 *)po = make_float2(o[0], o[1]);
+            else
+                *po = o[0];
+            if (d == 0) {
+                float *pml = a.part + (int64_t)a.p.n_tok * g.hq * ns * D;
+                pml[base * 2] = M;
+                pml[base * 2 + 1] = l;
             }
         }
-        if (own_new) store_new();  // one wave: it owns the newest key
     }
 }
 
@@ -551,21 +546,21 @@ __global__ void k_poison_fp8(PoolGeom g, int32_t n_layers, int64_t n_blocks,
     }
 }
 
-template <bool F8, int G>
+template <int D, bool F8, int G>
 hipError_t launch_mfma_g(const AttnArgs &a, hipStream_t s) {
     using S = MfmaShape<F8, G>;
     const int64_t units = (int64_t)a.p.n_tok * a.g.hkv * a.n_split;
     if (units == 0) return hipSuccess;
     if (units > INT32_MAX) return hipErrorInvalidValue;  // one grid dimension, 32-bit unit index
-    hipLaunchKernelGGL((k_attn_mfma<F8, G, S::NG, S::NBUF>), dim3((unsigned)units), dim3(64 * S::NG),
+    hipLaunchKernelGGL((k_attn_mfma<D, F8, G, S::NG, S::NBUF>), dim3((unsigned)units), dim3(64 * S::NG),
                        0, s, a);
     return hipGetLastError();
 }
-template <bool F8, int G>
+template <int D, bool F8, int G>
 int resident_mfma_g() {
     using S = MfmaShape<F8, G>;
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_mfma<F8, G, S::NG, S::NBUF>,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_attn_mfma<D, F8, G, S::NG, S::NBUF>,
                                                      64 * S::NG, 0) != hipSuccess)
         return 1;
     // The split rule fills these slots.  It counts the workgroups whose rings
@@ -577,26 +572,26 @@ int resident_mfma_g() {
     // at split 2, fp8 53.7 at split 2 against 60.8 unsplit.  (With more
     // streams in flight the decode ran slower: deeper rings, more waves per
     // unit, and fp8 split to fill the four workgroups its registers allow.)
-    constexpr int kRing = S::NG * S::NBUF * (F8 ? kF8Read : 2 * kBlock * kF8D * 2);
+    constexpr int kRing = S::NG * S::NBUF * (F8 ? kF8Read : 2 * kBlock * D * 2);
     constexpr int kTarget = ((64 << 10) + kRing / 2) / kRing;
     return std::min(std::max(n, 1), std::max(kTarget, 1));
 }
-template <bool F8>
+template <int D, bool F8>
 hipError_t launch_mfma(const AttnArgs &a, hipStream_t s) {
     switch (a.g.hq / a.g.hkv) {
-        case 1: return launch_mfma_g<F8, 1>(a, s);
-        case 2: return launch_mfma_g<F8, 2>(a, s);
-        case 4: return launch_mfma_g<F8, 4>(a, s);
-        default: return launch_mfma_g<F8, 8>(a, s);
+        case 1: return launch_mfma_g<D, F8, 1>(a, s);
+        case 2: return launch_mfma_g<D, F8, 2>(a, s);
+        case 4: return launch_mfma_g<D, F8, 4>(a, s);
+        default: return launch_mfma_g<D, F8, 8>(a, s);
     }
 }
-template <bool F8>
+template <int D, bool F8>
 int resident_mfma(int g) {
     switch (g) {
-        case 1: return resident_mfma_g<F8, 1>();
-        case 2: return resident_mfma_g<F8, 2>();
-        case 4: return resident_mfma_g<F8, 4>();
-        default: return resident_mfma_g<F8, 8>();
+        case 1: return resident_mfma_g<D, F8, 1>();
+        case 2: return resident_mfma_g<D, F8, 2>();
+        case 4: return resident_mfma_g<D, F8, 4>();
+        default: return resident_mfma_g<D, F8, 8>();
     }
 }
 
@@ -617,13 +612,17 @@ static_assert(MfmaShape<true, 1>::NG == MfmaShape<true, 4>::NG &&
                   MfmaShape<true, 2>::NG == MfmaShape<true, 4>::NG &&
                   MfmaShape<false, 8>::NG == MfmaShape<true, 8>::NG, "");
 
-int attn_fp8_resident_per_cu(int g) { return resident_mfma<true>(g); }
+int attn_fp8_resident_per_cu(int g) { return resident_mfma<kF8D, true>(g); }
 
-bool attn_mfma_bf16_supported(int d, int g) { return attn_fp8_supported(d, g); }
-int attn_mfma_bf16_resident_per_cu(int g) { return resident_mfma<false>(g); }
+bool attn_mfma_bf16_supported(int d, int g) {
+    return (d == 128 || d == 64) && (g == 1 || g == 2 || g == 4 || g == 8);
+}
+int attn_mfma_bf16_resident_per_cu(int d, int g) {
+    return d == 128 ? resident_mfma<128, false>(g) : resident_mfma<64, false>(g);
+}
 hipError_t launch_attn_mfma_bf16(const AttnArgs &a, hipStream_t s) {
     if (!attn_mfma_bf16_supported(a.g.d, a.g.hq / a.g.hkv)) return hipErrorInvalidValue;
-    return launch_mfma<false>(a, s);
+    return a.g.d == 128 ? launch_mfma<128, false>(a, s) : launch_mfma<64, false>(a, s);
 }
 
 hipError_t launch_append_fp8(const PoolGeom &g, const PlanView &p, int32_t layer, const void *k,
@@ -638,7 +637,7 @@ hipError_t launch_append_fp8(const PoolGeom &g, const PlanView &p, int32_t layer
 
 hipError_t launch_attn_fp8(const AttnArgs &a, hipStream_t s) {
     if (!attn_fp8_supported(a.g.d, a.g.hq / a.g.hkv)) return hipErrorInvalidValue;
-    return launch_mfma<true>(a, s);
+    return launch_mfma<kF8D, true>(a, s);
 }
 
 hipError_t launch_poison_fp8(const PoolGeom &g, int32_t n_layers, int64_t n_blocks,
