@@ -629,14 +629,15 @@ static __device__ __align__(256) float scratch[kScratchFloats];
 
 // merge split partials: one wave per (token, q head).  Lane s takes split s's
 // (max, sum); the splits' accumulators do not depend on them and are loaded in
-// the same round, eight splits at a time.  The maximum and the weighted sum
+// the same round, CH splits at a time.  The maximum and the weighted sum
 // are formed across the wave, and each split's weight is broadcast from its
-// lane.  (One memory round trip for up to eight splits, where a loop over the
-// splits first for the maximum and then for the sums took two.)
-template <typename T, int D>
+// lane.  Bound by memory round trips: one, with the output row loaded beside
+// the partials, for up to CH splits.  One session's frame, 768 merges of 32
+// splits, took 10.07 ms with rounds of eight splits and the row after them,
+// 9.69 ms so; at four splits (32 fp8 sessions) 4.959 against 4.941 ms.
+template <typename T, int D, int CH>
 __global__ __launch_bounds__(64) void k_merge(AttnArgs a) {
     constexpr int VD = D / 64;  // output dims per lane
-    constexpr int CH = 8;       // splits whose accumulators are in flight together
     const int64_t th = blockIdx.x;  // t * Hq + hq
     const int lane = threadIdx.x;
     const int ns = a.n_split;       // 2 .. 64
@@ -654,6 +655,8 @@ __global__ __launch_bounds__(64) void k_merge(AttnArgs a) {
     };
     load(0);
     const float2 ml0 = *(const float2 *)(pml + 2 * min(lane, ns - 1));  // lanes past ns: unused
+    const int t = (int)(blockIdx.x / (uint32_t)a.g.hq), hq = (int)blockIdx.x - t * a.g.hq;
+    const int64_t row = a.p.tok_row[t];
     __builtin_amdgcn_sched_barrier(0);  // every load above is in flight before the first wait
     const float2 ml = lane < ns ? ml0 : make_float2(-INFINITY, 0.f);
     float M = ml.x;
@@ -676,8 +679,6 @@ __global__ __launch_bounds__(64) void k_merge(AttnArgs a) {
             for (int r = 0; r < VD; ++r) acc[r] = fmaf(ws, part[c][r], acc[r]);
         }
     }
-    const int t = (int)(th / a.g.hq), hq = (int)(th % a.g.hq);
-    const int64_t row = a.p.tok_row[t];
     T *ob = (T *)a.out + (row * a.g.hq + hq) * D;
     const float inv = 1.f / Lsum;
 #pragma unroll
@@ -1735,19 +1736,32 @@ hipError_t launch_attn_valu(int dtype, const AttnArgs &a, hipStream_t s) {
     return a.g.d == 128 ? launch_valu_d<float, 128>(a, G, s) : launch_valu_d<float, 64>(a, G, s);
 }
 
+template <typename T, int D>
+void launch_merge_d(int64_t n, hipStream_t s, const AttnArgs &a) {
+    const dim3 grid((unsigned)n), block(64);
+    // the smallest round that takes every split: loads past n_split are wasted
+    // (64 splits take two rounds)
+    if (a.n_split <= 8)
+        hipLaunchKernelGGL((k_merge<T, D, 8>), grid, block, 0, s, a);
+    else if (a.n_split <= 16)
+        hipLaunchKernelGGL((k_merge<T, D, 16>), grid, block, 0, s, a);
+    else
+        hipLaunchKernelGGL((k_merge<T, D, 32>), grid, block, 0, s, a);
+}
+
 hipError_t launch_merge(int dtype, const AttnArgs &a, hipStream_t s) {
-    int64_t n = (int64_t)a.p.n_tok * a.g.hq;
+    const int64_t n = (int64_t)a.p.n_tok * a.g.hq;
     if (n == 0) return hipSuccess;
     if (dtype == 1) {
         if (a.g.d == 128)
-            hipLaunchKernelGGL((k_merge<bf16_t, 128>), dim3((unsigned)n), dim3(64), 0, s, a);
+            launch_merge_d<bf16_t, 128>(n, s, a);
         else
-            hipLaunchKernelGGL((k_merge<bf16_t, 64>), dim3((unsigned)n), dim3(64), 0, s, a);
+            launch_merge_d<bf16_t, 64>(n, s, a);
     } else {
         if (a.g.d == 128)
-            hipLaunchKernelGGL((k_merge<float, 128>), dim3((unsigned)n), dim3(64), 0, s, a);
+            launch_merge_d<float, 128>(n, s, a);
         else
-            hipLaunchKernelGGL((k_merge<float, 64>), dim3((unsigned)n), dim3(64), 0, s, a);
+            launch_merge_d<float, 64>(n, s, a);
     }
     return hipGetLastError();
 }

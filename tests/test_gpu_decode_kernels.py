@@ -54,3 +54,15 @@ def test_automatic_choice_around_its_line(g, n, d):
     """16 and 17 (head dim 64: 32 and 33) sessions of 32 KV heads: two (four)
     pairs per CU of 256, and one session more."""
     _run(g, 32, n, 0, 3, 2, d)
+
+
+@pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
+@pytest.mark.parametrize("n_split", [8, 9, 16, 17, 32])
+def test_merge_round_sizes(n_split, dtype, d):
+    """Splits at the edges of the merge's rounds of 8, 16 and 32."""
+    say(f"merge {n_split} splits {dtype} d={d}")
+    kw = dict(n_layers=1, hq=8, hkv=2, d=d, S=4, W=600, dtype=dtype)
+    pool = make_pool(**kw, cmax=200, max_sessions=2, n_blocks=110)
+    h = Harness(pool, n_sessions=2, **kw)
+    for f in range(4):
+        h.frame([200, 187], [2, 3], n_split=n_split)
