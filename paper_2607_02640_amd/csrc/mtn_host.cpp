@@ -32,6 +32,10 @@ constexpr int kSmallSlots = 16;
 constexpr int32_t kSmallWords = 2048;
 constexpr int kPfMinStages = 4;  // chunk prefill: stages (two blocks) of a key segment, at least
 constexpr int kPfMaxSplit = 16;  // ... and key segments of a pass, at most
+// fp32 chunk prefill, whose stages are single blocks of 0.5 to 0.9 us: blocks
+// of a key segment, at least, and blocks that a split has to save its pass
+constexpr int kPfMinBlocksF32 = 2;
+constexpr int kPfMinSavedF32 = 12;
 constexpr size_t kZeroPage = 2 * kBlock * 128 * 4;  // 16 KiB
 
 // Lowest-free-first block allocator over a bitmap (bit set = free).
@@ -380,6 +384,11 @@ int64_t keys_seen(const mtn_pool *P, int64_t t0, int64_t t1) {
 // unsplit) against 47.7 (256-row, 4 segments); 32 fp8 sessions 117.0 against
 // 94.2 (256-row, 2 segments); one session over 600 keys 20.0 against 15.4 at
 // 4 segments and 17.3 at 2.
+// The fp32 kernel's blocks take longer, so its segments go down to two of them,
+// but a short window is not split for less than the merge and its launch cost
+// (two-layer frames of 6 sessions, G = 2, D = 128, 18 blocks: 103.1 us at 2
+// segments, 91.9 at 4, 87.0 at 9; layer calls over 10 blocks at D = 64: 47.5
+// unsplit, 52.9 at 5).
 // 128-row passes make more workgroups but read every key twice as often: they
 // pay only while the split cannot fill the CUs about twice over (one session
 // 19.1 against 22.3 us with 256, four 27.0 against 29.0; sixteen lose, 57.3
@@ -400,8 +409,9 @@ void plan_prefill(mtn_pool *P) {
     for (int32_t i = 0; i < n_seq; ++i)
         blocks = std::max(blocks, ceil_div(keys_seen(P, P->seq_pos0[i], P->seq_pos0[i] + P->seq_ntok[i] - 1),
                                            kBlock));
-    const int64_t max_split = std::max<int64_t>(1, std::min<int64_t>(blocks / 2 / kPfMinStages, kPfMaxSplit));
     const bool f32 = P->cfg.kv_dtype == MTN_F32;  // its kernel has one pass size
+    const int64_t min_blocks = f32 ? kPfMinBlocksF32 : 2 * kPfMinStages;
+    const int64_t max_split = std::max<int64_t>(1, std::min<int64_t>(blocks / min_blocks, kPfMaxSplit));
     int64_t rpp = f32 ? prefill_f32_rows_per_pass()
                       : P->pf_rows_cfg ? P->pf_rows_cfg : prefill_rows_per_pass();
     if (!f32 && !P->pf_rows_cfg && P->n_cu > 0 && prefill_pass_rows_valid(128) &&
@@ -412,7 +422,7 @@ void plan_prefill(mtn_pool *P) {
     if (mfma && P->n_cu > 0) {
         const int64_t per = (int64_t)P->T * P->cfg.n_q_heads * (P->cfg.head_dim + 2);  // floats of a segment
         const int64_t ns = std::min<int64_t>({P->n_cu / passes(rpp), max_split, (int64_t)P->part_floats / per});
-        P->pf_split = (int32_t)std::max<int64_t>(1, ns);
+        if (ns > 1 && !(f32 && blocks - blocks / ns < kPfMinSavedF32)) P->pf_split = (int32_t)ns;
     }
     // one record per (sequence, row pass) with everything its workgroup
     // needs before the first copy, so that it takes one metadata load.

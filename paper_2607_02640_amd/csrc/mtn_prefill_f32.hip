@@ -169,9 +169,10 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_prefill_f32(F32Args pa) {
     // the row reference: starts at the lowest finite float, moves only when a
     // score exceeds it by more than 2^8 (probabilities stay <= 256)
     float m_ref = -3.402823466e38f, ls = 0.f;
-    f32x4_t acc[NC];
+    // two sums per output, over the even and the odd keys: chains half as long
+    f32x4_t acc[NC], acc1[NC];
 #pragma unroll
-    for (int dt = 0; dt < NC; ++dt) acc[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int dt = 0; dt < NC; ++dt) acc[dt] = acc1[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     auto step = [&](int st, auto masked_c) __attribute__((always_inline)) {
         constexpr bool MASKED = decltype(masked_c)::value;
@@ -189,21 +190,24 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_prefill_f32(F32Args pa) {
         float4 vf[NC];
 #pragma unroll
         for (int dt = 0; dt < NC; ++dt) vf[dt] = *(const float4 *)(sm + voff + dt * 1024);
-        f32x4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};  // two chains
+        // four chains of D / 4 products, as long as the vector kernel's sums
+        f32x4_t sq[4];
 #pragma unroll
-        for (int c = 0; c < NC; c += 2) {
-            s0 = mfma_f32(kf[c].x, q[c][0], s0);
-            s1 = mfma_f32(kf[c + 1].x, q[c + 1][0], s1);
-            s0 = mfma_f32(kf[c].y, q[c][1], s0);
-            s1 = mfma_f32(kf[c + 1].y, q[c + 1][1], s1);
-            s0 = mfma_f32(kf[c].z, q[c][2], s0);
-            s1 = mfma_f32(kf[c + 1].z, q[c + 1][2], s1);
-            s0 = mfma_f32(kf[c].w, q[c][3], s0);
-            s1 = mfma_f32(kf[c + 1].w, q[c + 1][3], s1);
+        for (int k = 0; k < 4; ++k) sq[k] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < NC; c += 4) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sq[k] = mfma_f32(kf[c + k].x, q[c + k][0], sq[k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sq[k] = mfma_f32(kf[c + k].y, q[c + k][1], sq[k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sq[k] = mfma_f32(kf[c + k].z, q[c + k][2], sq[k]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sq[k] = mfma_f32(kf[c + k].w, q[c + k][3], sq[k]);
         }
         float s[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) s[r] = s0[r] + s1[r];
+        for (int r = 0; r < 4; ++r) s[r] = (sq[0][r] + sq[1][r]) + (sq[2][r] + sq[3][r]);
         if constexpr (MASKED) {
             // slots of the block that this lane's query sees, and (for V)
             // those that any query of the pass may read: others may hold NaN
@@ -242,7 +246,10 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_prefill_f32(F32Args pa) {
             m_ref = mnew;
             ls *= alpha;
 #pragma unroll
-            for (int dt = 0; dt < NC; ++dt) acc[dt] *= alpha;
+            for (int dt = 0; dt < NC; ++dt) {
+                acc[dt] *= alpha;
+                acc1[dt] *= alpha;
+            }
         }
         float p[4];
 #pragma unroll
@@ -251,11 +258,11 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_prefill_f32(F32Args pa) {
 #pragma unroll
         for (int dt = 0; dt < NC; ++dt) acc[dt] = mfma_f32(vf[dt].x, p[0], acc[dt]);
 #pragma unroll
-        for (int dt = 0; dt < NC; ++dt) acc[dt] = mfma_f32(vf[dt].y, p[1], acc[dt]);
+        for (int dt = 0; dt < NC; ++dt) acc1[dt] = mfma_f32(vf[dt].y, p[1], acc1[dt]);
 #pragma unroll
         for (int dt = 0; dt < NC; ++dt) acc[dt] = mfma_f32(vf[dt].z, p[2], acc[dt]);
 #pragma unroll
-        for (int dt = 0; dt < NC; ++dt) acc[dt] = mfma_f32(vf[dt].w, p[3], acc[dt]);
+        for (int dt = 0; dt < NC; ++dt) acc1[dt] = mfma_f32(vf[dt].w, p[3], acc1[dt]);
     };
     // ring blocks that every row sees whole, as stages of the segment
     int full_lo = first_off == 0 ? 0 : 1;
@@ -275,6 +282,8 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_prefill_f32(F32Args pa) {
     if (!live) return;
     const float l = rows_sum(ls);  // every lane of the wave takes part
     if (!rv) return;
+#pragma unroll
+    for (int dt = 0; dt < NC; ++dt) acc[dt] += acc1[dt];
     if (ns > 1) {  // the segment's partial row (one that sees nothing of it: sum 0)
         const int64_t u = ((int64_t)(tok0 + tj) * g.hq + hq0 + gh) * ns + seg;
 #pragma unroll
