@@ -320,6 +320,11 @@ __device__ __forceinline__ float vmax3(float a, float b, float c) {
     return fmaxf(fmaxf(a, b), c);
 }
 __device__ __forceinline__ float vmax2(float a, float b) { return fmaxf(a, b); }
+// max of |a|, |b| and m, NaN if one of them is (one instruction)
+__device__ __forceinline__ float vmaxabs3(float a, float b, float m) {
+    return __builtin_elementwise_maximum(
+        __builtin_elementwise_maximum(__builtin_fabsf(a), __builtin_fabsf(b)), m);
+}
 // max over the four 16-lane rows (lanes with equal lane % 16)
 __device__ __forceinline__ float rows_max(float x) {
     return rows_pair<false, true>(rows_pair<false, false>(x));

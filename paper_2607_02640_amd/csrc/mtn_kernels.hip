@@ -852,6 +852,29 @@ struct PfBlock {
     bool sink;
 };
 
+// Eight E4M3 codes of a key row times the row's 2^e (byte: its stored
+// exponent) as bf16, and the codes of a dim's four keys times each key's 2^e;
+// every value exact.
+__device__ __forceinline__ uint4 f8_keys(const uint2 &c, uint32_t byte) {
+    // one scale for the whole row: the scaling conversion multiplies both
+    // codes of a pair by it
+    const float sk = __uint_as_float(byte << 23);
+    auto cv = [&](uint32_t w, auto hi) {
+        return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(
+                                                w, sk, decltype(hi)::value));
+    };
+    return make_uint4(cv(c.x, std::false_type{}), cv(c.x, std::true_type{}),
+                      cv(c.y, std::false_type{}), cv(c.y, std::true_type{}));
+}
+__device__ __forceinline__ uint2 f8_values(uint32_t w, uint32_t bytes) {
+    float sv[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) sv[r] = __uint_as_float(((bytes >> (8 * r)) & 0xFFu) << 23);
+    const auto lo = __builtin_amdgcn_cvt_pk_f32_fp8(w, false);
+    const auto hi = __builtin_amdgcn_cvt_pk_f32_fp8(w, true);
+    return make_uint2(pack_bf16x2(lo[0] * sv[0], lo[1] * sv[1]), pack_bf16x2(hi[0] * sv[2], hi[1] * sv[3]));
+}
+
 // An fp8 stage as the DMA lands it (two block regions of kF8Read bytes: K
 // codes, V codes in key quads, exponents) -> the bf16 stage layout above, each
 // value code * 2^e exactly.  512 threads: thread tid converts, in block
@@ -863,33 +886,16 @@ __device__ __forceinline__ void f8_stage_to_bf16(const uint8_t *src, uint8_t *ds
     {
         const int key = (tid >> 4) & 15, hc = tid & 15;
         const uint2 c = *(const uint2 *)(blk + key * kF8D + hc * 8);
-        // one scale for the whole row: the scaling conversion multiplies both
-        // codes of a pair by the key's 2^e, exactly
-        const float sk = __uint_as_float((uint32_t)blk[kF8Exp + key] << 23);
-        auto cv = [&](uint32_t w, auto hi) {
-            return __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(
-                                                    w, sk, decltype(hi)::value));
-        };
-        *(uint4 *)(dst + PfLds<kF8D>::k(b, key, hc)) =
-            make_uint4(cv(c.x, std::false_type{}), cv(c.x, std::true_type{}),
-                       cv(c.y, std::false_type{}), cv(c.y, std::true_type{}));
+        *(uint4 *)(dst + PfLds<kF8D>::k(b, key, hc)) = f8_keys(c, blk[kF8Exp + key]);
     }
     {
         const int kg = (tid >> 6) & 3, dp = tid & 63;
         const uint2 c = *(const uint2 *)(blk + kF8Tile + (kg * kF8D + 2 * dp) * 4);
         const uint32_t ew = *(const uint32_t *)(blk + kF8Exp + kBlock + 4 * kg);
-        float sv[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sv[r] = __uint_as_float(((ew >> (8 * r)) & 0xFFu) << 23);
         const uint32_t w[2] = {c.x, c.y};
 #pragma unroll
-        for (int x = 0; x < 2; ++x) {  // dim 2 dp + x: keys 4 kg .. 4 kg + 3
-            const auto lo = __builtin_amdgcn_cvt_pk_f32_fp8(w[x], false);
-            const auto hi = __builtin_amdgcn_cvt_pk_f32_fp8(w[x], true);
-            *(uint2 *)(dst + PfLds<kF8D>::v16(b, 2 * dp + x, kg >> 1) + (kg & 1) * 8) =
-                make_uint2(pack_bf16x2(lo[0] * sv[0], lo[1] * sv[1]),
-                           pack_bf16x2(hi[0] * sv[2], hi[1] * sv[3]));
-        }
+        for (int x = 0; x < 2; ++x)  // dim 2 dp + x: keys 4 kg .. 4 kg + 3
+            *(uint2 *)(dst + PfLds<kF8D>::v16(b, 2 * dp + x, kg >> 1) + (kg & 1) * 8) = f8_values(w[x], ew);
     }
 }
 
@@ -1326,6 +1332,12 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
                          ((kb >= mb.lo && kb < mb.hi) ? 0xFFFF0000u : 0u);
             }
         };
+        // slots of a block that a query at position tq sees: one range
+        auto row_slots = [&](const PfBlock &mb, int tq, int &vlo, int &vhi) __attribute__((always_inline)) {
+            const int wl = g.window < 0 ? -(1 << 30) : tq - g.window + 1;
+            vlo = mb.sink ? mb.lo : max(mb.lo, wl - mb.p0);
+            vhi = min(mb.hi, tq + 1 - mb.p0);
+        };
         // lane l holds row ln16 and stage keys 8 lg + r (sa) and 8 lg + 4 + r
         // (sb), r < 4: slots lkey0 + r and lkey0 + 4 + r of block lblk.
         // Scores of slots the row's query cannot see become -inf.
@@ -1333,14 +1345,10 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
                                __attribute__((always_inline)) {
             constexpr int NT = decltype(nt_c)::value;
             const PfBlock mb = vblock(2 * st + lblk);
-            const int bp0 = mb.p0, blo = mb.lo, bhi = mb.hi;
 #pragma unroll
             for (int i = 0; i < NT; ++i) {
-                // visible slots of the block for query position tq: one range
-                const int tq = tq_i[i];
-                const int wl = g.window < 0 ? -(1 << 30) : tq - g.window + 1;
-                const int vlo = mb.sink ? blo : max(blo, wl - bp0);
-                const int vhi = min(bhi, tq + 1 - bp0);
+                int vlo, vhi;
+                row_slots(mb, tq_i[i], vlo, vhi);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const int oa = lkey0 + r, ob = oa + 4;
@@ -1591,6 +1599,130 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
         // no DMA may land in LDS after the workgroup has ended
         if (dma_wave) vm_wait<0>();
 
+        // A key that some row of a tile sees and another does not has probability
+        // 0 in the second one's column of the PV product, and 0 * Inf is NaN.  A
+        // tile that ends with a non-finite sum is therefore computed once more,
+        // stage by stage with its operands straight from the pool and V zeroed,
+        // token by token (a token's G rows lie in one tile), past what each sees:
+        // the same sums for every other row.  (A test of the V words in the
+        // masked stages instead, with the product apart there, spilled 66
+        // registers at D = 128.)
+        auto apart = [&](auto ic) __attribute__((always_inline)) {
+            constexpr int i = decltype(ic)::value;
+            m_ref[i] = -3.402823466e38f;
+            msh[i] = 0.f;
+            l_i[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            ls[i] = 0.f;
+#pragma unroll
+            for (int dt = 0; dt < NT16; ++dt) acc[i][dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            int ln = ln16;  // (nothing of the products below is kept through the stage loops)
+            asm volatile("" : "+v"(ln));
+            const int kap = 8 * (ln >> 2) + (ln & 3);  // the first QK MFMA's key of this lane
+#pragma nounroll
+            for (int st = 0; st < n_stages; ++st) {
+                const int ph0 = phys(2 * st), ph1 = phys(2 * st + 1);
+                auto at = [&](int b) {
+                    const int ph = b ? ph1 : ph0;
+                    return ph >= 0 ? layer_base + (int64_t)ph * g.block_stride : pa.zero_page;
+                };
+                const uint8_t *kb = at(kap >> 4), *vb = at(lblk);
+                f32x4_t s0 = {-msh[i], -msh[i], -msh[i], -msh[i]}, s1 = s0;
+#pragma unroll
+                for (int s = 0; s < ND; ++s) {
+                    uint4 k2[2];
+#pragma unroll
+                    for (int x = 0; x < 2; ++x) {
+                        const int key = (kap & 15) + 4 * x;
+                        if constexpr (F8)
+                            k2[x] = f8_keys(*(const uint2 *)(kb + key * D + (s * 4 + lg) * 8), kb[kF8Exp + key]);
+                        else
+                            k2[x] = ((const uint4 *)(kb + key * Lds::kRow))[s * 4 + lg];
+                    }
+                    s0 = mfma16x16x32(k2[0], qf[i][s], s0);
+                    s1 = mfma16x16x32(k2[1], qf[i][s], s1);
+                }
+                const PfBlock mb = vblock(2 * st + lblk);
+                int vlo, vhi;
+                row_slots(mb, tq_i[i], vlo, vhi);
+                float sc[8], p[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const int slot = lkey0 + e;
+                    sc[e] = slot >= vlo && slot < vhi ? (e < 4 ? s0[e] : s1[e - 4]) : -INFINITY;
+                }
+                const float m8 = vmax3(vmax3(sc[0], sc[1], sc[2]), vmax3(sc[3], sc[4], sc[5]),
+                                       vmax3(sc[6], sc[7], sc[0]));
+                const float mx = rows_max(m8) + msh[i];
+                const bool up = mx > m_ref[i] + kLazy;
+                const float mnew = up ? mx : m_ref[i];
+                const float alpha = up ? __builtin_amdgcn_exp2f(m_ref[i] - mnew) : 1.f;
+                m_ref[i] = mnew;
+                if constexpr (kShift) {
+                    const float dsh = up ? mnew - msh[i] : 0.f;
+                    msh[i] = up ? mnew : msh[i];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) sc[e] -= dsh;
+                }
+                l_i[i] *= alpha;
+                ls[i] *= alpha;
+#pragma unroll
+                for (int dt = 0; dt < NT16; ++dt) acc[i][dt] *= alpha;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(kShift ? sc[e] : sc[e] - m_ref[i]);
+                const uint4 pb = make_uint4(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]),
+                                            pack_bf16x2(p[4], p[5]), pack_bf16x2(p[6], p[7]));
+                if constexpr (kMfmaSum)
+                    l_i[i] = mfma16x16x32(make_uint4(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u),
+                                          pb, l_i[i]);
+                else
+                    ls[i] += ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+#pragma nounroll
+                for (int r0 = 0; r0 < 16; r0 += G) {
+                    int tlo, thi;
+                    row_slots(mb, __builtin_amdgcn_readlane(tq_i[i], r0), tlo, thi);
+                    uint32_t vm[4];
+#pragma unroll
+                    for (int q4 = 0; q4 < 4; ++q4) {
+                        const int ka = lkey0 + 2 * q4;
+                        vm[q4] = ((ka >= tlo && ka < thi) ? 0x0000FFFFu : 0u) |
+                                 ((ka + 1 >= tlo && ka + 1 < thi) ? 0xFFFF0000u : 0u);
+                    }
+                    const bool mine = ln >= r0 && ln < r0 + G;
+#pragma unroll
+                    for (int dt = 0; dt < NT16; ++dt) {
+                        const int d = dt * 16 + ln;
+                        uint4 v;
+                        if constexpr (F8) {
+                            const uint8_t *vq = vb + kF8Tile + ((lkey0 >> 2) * D + d) * 4;
+                            const uint8_t *ve = vb + kF8Exp + kBlock + lkey0;
+                            const uint2 w0 = f8_values(*(const uint32_t *)vq, *(const uint32_t *)ve);
+                            const uint2 w1 = f8_values(*(const uint32_t *)(vq + 4 * D),
+                                                       *(const uint32_t *)(ve + 4));
+                            v = make_uint4(w0.x, w0.y, w1.x, w1.y);
+                        } else {
+                            v = ((const uint4 *)(vb + Lds::kTile + d * 32))[lg & 1];
+                        }
+                        v = make_uint4(v.x & vm[0], v.y & vm[1], v.z & vm[2], v.w & vm[3]);
+                        const f32x4_t t = mfma16x16x32(v, pb, acc[i][dt]);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[i][dt][e] = mine ? t[e] : acc[i][dt][e];
+                    }
+                }
+            }
+        };
+        auto finite = [&](int i) {
+            float m[2] = {0.f, 0.f};
+#pragma unroll
+            for (int dt = 0; dt < NT16; ++dt)
+#pragma unroll
+                for (int e = 0; e < 2; ++e)
+                    m[e] = vmaxabs3(acc[i][dt][2 * e], acc[i][dt][2 * e + 1], m[e]);
+            return __builtin_amdgcn_ballot_w64(!(vmaxabs3(m[0], m[1], 0.f) < INFINITY)) == 0;
+        };
+        if (__builtin_expect(live[0] && !finite(0), 0)) apart(std::integral_constant<int, 0>{});
+        if constexpr (kPfTpw == 2)
+            if (__builtin_expect(live[1] && !finite(1), 0)) apart(std::integral_constant<int, 1>{});
+
         // ---- epilogue: normalise and write rows of this pass, or leave the
         // segment's partial rows (a segment that a row sees nothing of: sum 0)
 #pragma unroll
@@ -1598,7 +1730,10 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
             if (!live[i]) continue;
             // (every lane of the wave takes part in the row sum)
             const float lt = kMfmaSum ? l_i[i][0] : rows_sum(ls[i]);
-            const int r = pass_row0 + (wv + kPfWaves * i) * 16 + ln16;
+            // (computed again: kept from the prologue, j and gh were spilled, fp8)
+            int ln = ln16;
+            asm volatile("" : "+v"(ln));
+            const int r = pass_row0 + (wv + kPfWaves * i) * 16 + ln;
             if (r >= pass_end) continue;
             const int j = r / G, gh = r % G;
             if (ns > 1) {

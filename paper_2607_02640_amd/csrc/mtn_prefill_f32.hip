@@ -168,28 +168,23 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_prefill_f32(F32Args pa) {
 
     // the row reference: starts at the lowest finite float, moves only when a
     // score exceeds it by more than 2^8 (probabilities stay <= 256)
-    float m_ref = -3.402823466e38f, ls = 0.f;
+    float m_ref, ls;
     // two sums per output, over the even and the odd keys: chains half as long
     f32x4_t acc[NC], acc1[NC];
+    auto reset = [&]() __attribute__((always_inline)) {
+        m_ref = -3.402823466e38f;
+        ls = 0.f;
 #pragma unroll
-    for (int dt = 0; dt < NC; ++dt) acc[dt] = acc1[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int dt = 0; dt < NC; ++dt) acc[dt] = acc1[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    };
+    reset();
 
-    auto step = [&](int st, auto masked_c) __attribute__((always_inline)) {
-        constexpr bool MASKED = decltype(masked_c)::value;
-        // this wave's share of the stage has landed; the barrier covers the
-        // other shares and frees the slot last read at st - 1
-        vm_wait<NPW * (NS - 2)>();
-        __syncthreads();
-        issue(st + NS - 1, nph);
-        nph = phys(st + NS);
-        if (!live) return;
-        const uint8_t *sm = &ring[st % NS][0];
-        float4 kf[NC];
-#pragma unroll
-        for (int c = 0; c < NC; ++c) kf[c] = *(const float4 *)(sm + koff[c]);
-        float4 vf[NC];
-#pragma unroll
-        for (int dt = 0; dt < NC; ++dt) vf[dt] = *(const float4 *)(sm + voff + dt * 1024);
+    // Scores, softmax and PV of block st from its fragments.  APART: the PV
+    // product is taken token by token (a token's G rows lie in one tile), V
+    // zeroed past what each sees.
+    auto block = [&](int st, const float4 (&kf)[NC], float4 (&vf)[NC], auto masked_c, auto apart_c)
+                     __attribute__((always_inline)) {
+        constexpr bool MASKED = decltype(masked_c)::value, APART = decltype(apart_c)::value;
         // four chains of D / 4 products, as long as the vector kernel's sums
         f32x4_t sq[4];
 #pragma unroll
@@ -205,14 +200,15 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_prefill_f32(F32Args pa) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) sq[k] = mfma_f32(kf[c + k].w, q[c + k][3], sq[k]);
         }
+        int vlo = 0, vhi = kBlock;  // the slots of the block that this lane's query sees
         float s[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) s[r] = (sq[0][r] + sq[1][r]) + (sq[2][r] + sq[3][r]);
         if constexpr (MASKED) {
-            // slots of the block that this lane's query sees, and (for V)
-            // those that any query of the pass may read: others may hold NaN
+            // [lo, hi): the slots that any query of the pass sees; V of others may
+            // hold NaN
             const int v = v0 + st;
-            int lo = 0, hi = kBlock, vlo = 0, vhi = kBlock;
+            int lo = 0, hi = kBlock;
             if (v < n_sb) {
                 hi = min(kBlock, sink_tokens - v * kBlock);
                 vhi = min(hi, tq + 1 - v * kBlock);
@@ -255,6 +251,30 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_prefill_f32(F32Args pa) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(s[r] - m_ref);
         ls += (p[0] + p[1]) + (p[2] + p[3]);
+        if constexpr (APART) {
+#pragma nounroll
+            for (int t0 = 0; t0 < 16; t0 += G) {
+                const int tlo = __builtin_amdgcn_readlane(vlo, t0);
+                const int thi = __builtin_amdgcn_readlane(vhi, t0);
+                const bool mine = ln16 >= t0 && ln16 < t0 + G;
+#pragma unroll
+                for (int dt = 0; dt < NC; ++dt) {
+                    const float vw[4] = {vf[dt].x, vf[dt].y, vf[dt].z, vf[dt].w};
+                    f32x4_t t[2] = {acc[dt], acc1[dt]};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int key = 4 * lg + e;
+                        t[e & 1] = mfma_f32(key >= tlo && key < thi ? vw[e] : 0.f, p[e], t[e & 1]);
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        acc[dt][r] = mine ? t[0][r] : acc[dt][r];
+                        acc1[dt][r] = mine ? t[1][r] : acc1[dt][r];
+                    }
+                }
+            }
+            return;
+        }
 #pragma unroll
         for (int dt = 0; dt < NC; ++dt) acc[dt] = mfma_f32(vf[dt].x, p[0], acc[dt]);
 #pragma unroll
@@ -263,6 +283,23 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_prefill_f32(F32Args pa) {
         for (int dt = 0; dt < NC; ++dt) acc[dt] = mfma_f32(vf[dt].z, p[2], acc[dt]);
 #pragma unroll
         for (int dt = 0; dt < NC; ++dt) acc1[dt] = mfma_f32(vf[dt].w, p[3], acc1[dt]);
+    };
+    auto step = [&](int st, auto masked_c) __attribute__((always_inline)) {
+        // this wave's share of the stage has landed; the barrier covers the
+        // other shares and frees the slot last read at st - 1
+        vm_wait<NPW * (NS - 2)>();
+        __syncthreads();
+        issue(st + NS - 1, nph);
+        nph = phys(st + NS);
+        if (!live) return;
+        const uint8_t *sm = &ring[st % NS][0];
+        float4 kf[NC];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) kf[c] = *(const float4 *)(sm + koff[c]);
+        float4 vf[NC];
+#pragma unroll
+        for (int dt = 0; dt < NC; ++dt) vf[dt] = *(const float4 *)(sm + voff + dt * 1024);
+        block(st, kf, vf, masked_c, std::false_type{});
     };
     // ring blocks that every row sees whole, as stages of the segment
     int full_lo = first_off == 0 ? 0 : 1;
@@ -280,6 +317,30 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_prefill_f32(F32Args pa) {
     vm_wait<0>();  // no DMA may land in LDS after the workgroup has ended
 
     if (!live) return;
+    // A key that some row of the tile sees and another does not has probability 0
+    // in the second one's column of the PV product, and 0 * Inf is NaN.  A tile
+    // that ends with a non-finite sum is therefore computed once more, block by
+    // block from memory with each token's V apart: the same sums for every other
+    // row.  A finite tile pays for the test alone (D / 4 instructions).
+    float m[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int dt = 0; dt < NC; ++dt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) m[r] = vmaxabs3(acc[dt][r], acc1[dt][r], m[r]);
+    if (__builtin_amdgcn_ballot_w64(!(vmaxabs3(m[0], m[1], vmaxabs3(m[2], m[3], 0.f)) < INFINITY))) {
+        reset();
+#pragma nounroll
+        for (int st = 0; st < nst; ++st) {
+            const uint8_t *src = base + (int64_t)phys(st) * g.block_stride;
+            float4 kf[NC], vf[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) kf[c] = ((const float4 *)(src + ln16 * ROW))[4 * c + lg];
+#pragma unroll
+            for (int dt = 0; dt < NC; ++dt)
+                vf[dt] = ((const float4 *)(src + TILE + (16 * dt + ln16) * 64))[lg];
+            block(st, kf, vf, std::true_type{}, std::true_type{});
+        }
+    }
     const float l = rows_sum(ls);  // every lane of the wave takes part
     if (!rv) return;
 #pragma unroll
