@@ -320,6 +320,15 @@ __device__ __forceinline__ float vmax3(float a, float b, float c) {
     return fmaxf(fmaxf(a, b), c);
 }
 __device__ __forceinline__ float vmax2(float a, float b) { return fmaxf(a, b); }
+// Natural log-sum-exp of a row from its log2 reference m and its sum l relative
+// to it.  The logarithm is taken of l's mantissa: its error is a unit in the
+// last place, which of log2(l) would grow with the distance that a reference
+// moving in steps of 2^8 leaves between m and the row's maximum.
+__device__ __forceinline__ float row_lse(float m, float l) {
+    constexpr float kLn2 = 0.6931471805599453f;
+    return fmaf((float)__builtin_amdgcn_frexp_expf(l), kLn2,
+                (m + __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(l))) * kLn2);
+}
 // max of |a|, |b| and m, NaN if one of them is (one instruction)
 __device__ __forceinline__ float vmaxabs3(float a, float b, float m) {
     return __builtin_elementwise_maximum(

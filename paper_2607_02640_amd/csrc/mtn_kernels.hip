@@ -684,7 +684,7 @@ __global__ __launch_bounds__(64) void k_merge(AttnArgs a) {
 #pragma unroll
     for (int r = 0; r < VD; ++r) ob[lane * VD + r] = from_f32<T>(acc[r] * inv);
     if (a.lse && lane == 0)
-        a.lse[row * a.g.hq + hq] = (M + __builtin_amdgcn_logf(Lsum)) * 0.6931471805599453f;
+        a.lse[row * a.g.hq + hq] = row_lse(M, Lsum);
 }
 
 // ---------------------------------------------------------------------------

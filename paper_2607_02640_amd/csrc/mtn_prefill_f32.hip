@@ -170,6 +170,9 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_prefill_f32(F32Args pa) {
     // score exceeds it by more than 2^8 (probabilities stay <= 256)
     float m_ref, ls;
     // two sums per output, over the even and the odd keys: chains half as long
+    // (error against 64 bits of 22 unsplit sessions over 1500 keys 7.2e-7 with
+    // one, 5.3e-7 with two, the vector kernel's 5.2e-7; a frame of 13 sessions
+    // 332.7 us with one, 333.0 with two)
     f32x4_t acc[NC], acc1[NC];
     auto reset = [&]() __attribute__((always_inline)) {
         m_ref = -3.402823466e38f;
@@ -359,7 +362,7 @@ __global__ __launch_bounds__(64 * kF32Waves) void k_prefill_f32(F32Args pa) {
 #pragma unroll
     for (int dt = 0; dt < NC; ++dt)
         *(f32x4_t *)((float *)a.out + oh * D + 16 * dt + 4 * lg) = acc[dt] * inv;
-    if (a.lse && lg == 0) a.lse[oh] = (m_ref + __builtin_amdgcn_logf(l)) * 0.6931471805599453f;
+    if (a.lse && lg == 0) a.lse[oh] = row_lse(m_ref, l);
 }
 
 template <int D>
