@@ -1174,15 +1174,23 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
         uint4 qf[kPfTpw][ND];
         f32x4_t acc[kPfTpw][NT16];
         // row reference max (log2 units) and the row sum of the probabilities.
-        // bf16 pool: the sum of their bf16 roundings, accumulated by an MFMA
-        // against all-ones (every entry = the row sum).  fp8 pool: ls holds
+        // bf16 pool, D = 128: the sum of their bf16 roundings, accumulated by an MFMA
+        // against all-ones (every entry = the row sum).  Otherwise ls holds
         // the lane's part of the fp32 sum (its eight keys of every
-        // stage), the four lanes of a row added in the epilogue; vector adds
-        // in place of that MFMA free registers the fp8 stage loop otherwise
-        // spills (2-3 % per layer; the bf16 kernel measured no gain).  The reference starts at the lowest finite float: the first finite
+        // stage), the four lanes of a row added in the epilogue.  fp8: vector adds
+        // in place of that MFMA free registers the stage loop otherwise
+        // spills (2-3 % per layer; the D = 128 bf16 kernel measured no gain).
+        // D = 64: the vector kernel that ran these chunks before summed
+        // unrounded probabilities too (frames of 21 sessions 401 against 404 us).
+        // The reference starts at the lowest finite float: the first finite
         // score of a row exceeds it by more than 2^8 and sets it, while
         // masked (-inf) scores give probability 0 against it.
         float m_ref[kPfTpw];
+        // How far a score may exceed the reference (log2 units) before it moves.
+        // At 0, D = 64, the reference is the running maximum and the largest
+        // probability 1, exact in bf16, as the vector kernel had it: with 2^8 the
+        // outputs' error was 2-3 % larger (frames of 21 sessions 404 against 414 us).
+        constexpr float kLazy = D == 64 ? 0.f : 8.f;
         // bf16 pool: the QK MFMAs start their accumulators at -msh, so the
         // scores come out already shifted by the reference and each
         // probability is one exponential with no subtraction; thr is the bump
@@ -1194,7 +1202,7 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
         constexpr bool kShift = !F8;
         float msh[kPfTpw], thr[kPfTpw];
         f32x4_t csh[kPfTpw];  // {-msh} x 4, kept so the QK start needs no moves
-        constexpr bool kMfmaSum = !F8;
+        constexpr bool kMfmaSum = !F8 && D == 128;
         f32x4_t l_i[kPfTpw];
         float ls[kPfTpw];
         int tq_i[kPfTpw];
@@ -1222,7 +1230,7 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
             m_ref[i] = -3.402823466e38f;
             msh[i] = 0.f;
             csh[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            thr[i] = m_ref[i] + 8.f;
+            thr[i] = m_ref[i] + kLazy;
             l_i[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             ls[i] = 0.f;
 #pragma unroll
@@ -1303,12 +1311,11 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
         // masks and softmaxes the scores of stage st (computed by the previous
         // iteration) while the QK MFMAs of stage st + 1 run, then accumulates
         // PV of stage st.  The softmax keeps a per-row reference max that
-        // moves only when a score exceeds it by more than 2^8 (probabilities
-        // stay <= 256), so the accumulator rescale is rare; the result is the
-        // same softmax.  Whether any lane holds such a score is checked on
+        // moves only when a score exceeds it by more than 2^kLazy (at 8,
+        // probabilities stay <= 256 and the accumulator rescale is rare); the
+        // result is the same softmax.  Whether any lane holds such a score is checked on
         // the lane's own eight scores; only then is the row max formed across
         // the four lanes of a row.
-        constexpr float kLazy = 8.f;
         // the bf16 stage buffer the MFMAs read for stage st
         auto stage_buf = [&](int st) -> uint8_t * {
             if constexpr (F8)
@@ -1654,19 +1661,23 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
                                        vmax3(sc[6], sc[7], sc[0]));
                 const float mx = rows_max(m8) + msh[i];
                 const bool up = mx > m_ref[i] + kLazy;
-                const float mnew = up ? mx : m_ref[i];
-                const float alpha = up ? __builtin_amdgcn_exp2f(m_ref[i] - mnew) : 1.f;
-                m_ref[i] = mnew;
-                if constexpr (kShift) {
-                    const float dsh = up ? mnew - msh[i] : 0.f;
-                    msh[i] = up ? mnew : msh[i];
+                // (a branch as in the stage loop: in one block the compiler may fuse
+                // the rescale into the sums)
+                if (__builtin_amdgcn_ballot_w64(up)) {
+                    const float mnew = up ? mx : m_ref[i];
+                    const float alpha = up ? __builtin_amdgcn_exp2f(m_ref[i] - mnew) : 1.f;
+                    m_ref[i] = mnew;
+                    if constexpr (kShift) {
+                        const float dsh = up ? mnew - msh[i] : 0.f;
+                        msh[i] = up ? mnew : msh[i];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) sc[e] -= dsh;
+                        for (int e = 0; e < 8; ++e) sc[e] -= dsh;
+                    }
+                    l_i[i] *= alpha;
+                    ls[i] *= alpha;
+#pragma unroll
+                    for (int dt = 0; dt < NT16; ++dt) acc[i][dt] *= alpha;
                 }
-                l_i[i] *= alpha;
-                ls[i] *= alpha;
-#pragma unroll
-                for (int dt = 0; dt < NT16; ++dt) acc[i][dt] *= alpha;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(kShift ? sc[e] : sc[e] - m_ref[i]);
                 const uint4 pb = make_uint4(pack_bf16x2(p[0], p[1]), pack_bf16x2(p[2], p[3]),

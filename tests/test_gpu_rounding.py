@@ -82,3 +82,59 @@ def test_fp32_chunk_log_sum_exp_when_the_reference_lags():
     rms = float(np.sqrt(np.mean(np.concatenate(err) ** 2)))
     say(f"rms {rms:.2e}")
     assert rms < 4e-7
+
+
+@pytest.mark.parametrize("g", [1, 8])
+def test_head_dim_64_chunk_sums_unrounded_probabilities(g):
+    """The log-sum-exp of bf16 chunks at head dimension 64: sums in fp32 of
+    probabilities in fp32 (2e-6 covers 50 of them, the exponentials and the
+    result's last place); probabilities rounded to bf16 first are up to 2e-3
+    off each."""
+    say(f"D=64 chunk row sums G={g}")
+    rng = np.random.default_rng(g)
+    for n in (24, 41, 50):
+        keys = rng.integers(-256, 257, n) / 128.0
+        v = torch.from_numpy(rng.standard_normal((n, 64)))
+        _, lse, _, want = _attend("bf16", 64, g, 2, keys, v, [8.0, 7.0, 6.5, 8.0], "chunk")
+        err = float((lse[0] - want[:, None]).abs().max())
+        say(f"n={n} err {err:.2e}")
+        assert err < 2e-6
+
+
+def _dominant(dtype, d, q):
+    """A key whose probability 2^(q' k) is as far from bf16 as they get, just
+    under 2^8."""
+    qs, best = _scaled_query(q, d, dtype), (0.0, 0.0)
+    for i in range(256):
+        k = float(torch.tensor(4.0 + i / 32).bfloat16())
+        p = 2.0 ** (qs * k)
+        if 64.0 < p < 250.0:
+            best = max(best, (abs(float(torch.tensor(p).bfloat16()) / p - 1.0), k))
+    assert best[0] > 0.002
+    return best[1], 2.0 ** (qs * best[1])
+
+
+@pytest.mark.parametrize("how,d,g,kernel", [
+    ("chunk", 64, 1, 0), ("chunk", 64, 8, 0),
+])
+def test_the_largest_probability_is_exact(how, d, g, kernel):
+    """One key carries nearly all of the weight, and a key of 2^-7 of it sets
+    the reference a block before.  With the reference at the maximum the large
+    probability is 1, and the output is the float64 one rounded once: within
+    half a unit in its last place and the small weight's own rounding.  Against
+    the earlier reference it would be rounded too, by 2e-3."""
+    say(f"dominant key {how} d={d} G={g}")
+    rng = np.random.default_rng(d + g)
+    n, step = 416, 32 if how == "chunk" else 16
+    top, weight = _dominant("bf16", d, 8.0)
+    for at in range(4):
+        keys = np.full(n, -30.0)
+        pos = 133 + at * step
+        keys[pos - step], keys[pos] = 0.0, top
+        v = torch.from_numpy(rng.uniform(1.0, 2.0, (n, d)) * rng.choice([-1.0, 1.0], (n, d)))
+        q = [8.0] * (3 if how == "chunk" else 1)
+        out, _, want, _ = _attend("bf16", d, g, 2, keys, v, q, how, kernel=kernel)
+        ulp = torch.exp2(torch.floor(torch.log2(want.abs())) - 7)
+        err = ((out[0] - want[:, None]).abs() - 0.5 * ulp[:, None]).max()
+        say(f"position {pos}: {float(err):.2e} past half a unit")
+        assert err <= 2.0 / weight * 2.0 ** -8 + 1e-6
