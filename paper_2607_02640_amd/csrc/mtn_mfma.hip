@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256) void k_append_fp8(PoolGeom g, PlanView p, int3
 // accumulators are dims D/4 g4 + D/16 i + j (i < 4, j < D/16) -- the PV MFMA j
 // takes dims D/16 m + j on its rows m.  The online softmax keeps a per-head
 // reference max that moves only when a block's max exceeds it by more than
-// 2^8, so the accumulator rescale is rare.  At the end the waves' (max, sum,
+// kLag (in log2 units; at 8 the accumulator rescale is rare).  At the end the waves' (max, sum,
 // acc) are merged through LDS by log-sum-exp.
 // Launch shape, from sweeps of waves per workgroup (2..8) and ring depth
 // (2..4) at the 128-session G = 8 (512 units per launch), 64-session G = 1
@@ -275,8 +275,13 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
         wave_sync();
     };
 
+    // How far a score may exceed the head's reference (log2 units) before it
+    // moves.  At 0 the reference is the running maximum and the largest
+    // probability 1, exact in bf16, as in the vector kernel that ran these
+    // launches before: with 8 the outputs' error was 1.5-5 % larger.
+    constexpr float kLag = F8 || (D == 128 && G == 8) ? 8.f : 0.f;
     // the reference starts at the lowest finite float: the first finite score
-    // exceeds it by more than 2^8 and sets it, masked (-inf) scores give 0
+    // exceeds it by more than kLag and sets it, masked (-inf) scores give 0
     float m_ref = -3.402823466e38f, lsum = 0.f;
     f32x4_t acc[NJ];
 #pragma unroll
@@ -353,7 +358,7 @@ __global__ __launch_bounds__(64 * NG) void k_attn_mfma(AttnArgs a) {
             }
         }
         const float mx = rows_max(vmax3(vmax3(sc[0], sc[1], sc[2]), sc[3], sc[0]));
-        const bool bump = mx > m_ref + 8.f;
+        const bool bump = mx > m_ref + kLag;
         if (__builtin_amdgcn_ballot_w64(bump)) {
             const float mnew = bump ? mx : m_ref;
             const float alpha = mnew == m_ref ? 1.f : __builtin_amdgcn_exp2f(m_ref - mnew);

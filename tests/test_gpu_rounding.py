@@ -116,6 +116,10 @@ def _dominant(dtype, d, q):
 
 @pytest.mark.parametrize("how,d,g,kernel", [
     ("chunk", 64, 1, 0), ("chunk", 64, 8, 0),
+    # the matrix-core decode where it took over from the vector kernel
+    ("decode", 64, 1, 0), ("decode", 64, 4, 0), ("decode", 64, 8, 0),
+    ("decode", 128, 1, 0), ("decode", 128, 2, 0), ("decode", 128, 4, 0),
+    ("decode", 128, 4, 1),
 ])
 def test_the_largest_probability_is_exact(how, d, g, kernel):
     """One key carries nearly all of the weight, and a key of 2^-7 of it sets
