@@ -1,7 +1,7 @@
 """GPU parity of the bf16 decode kernels on both sides of the automatic choice
 at G < 8 (the matrix-core kernel up to two, at head dim 64 four, (query, KV
-head) pairs per CU, the vector kernel beyond), and of the vector kernel at the small batches that only
-a forced choice gives it."""
+head) pairs per CU, the vector kernel beyond), and of the vector kernel at the
+small batches that only a forced choice gives it."""
 import random
 
 import pytest
@@ -12,15 +12,21 @@ from tests._gpu_util import Harness, make_pool, say
 pytestmark = pytest.mark.gpu
 
 
-def _run(g, hkv, n, kind, frames, decodes, d=128):
+def _kw(g, hkv, d):
+    return dict(n_layers=1, hq=hkv * g, hkv=hkv, d=d, S=4, W=70, dtype="bf16")
+
+
+def _run(g, hkv, n, kind, frames, decodes, d=128, every=False):
+    """Frames against the oracle; every: all sessions decode in every round."""
     say(f"bf16 decode d={d} G={g} hkv={hkv} sessions={n} kernel={kind}")
-    kw = dict(n_layers=1, hq=hkv * g, hkv=hkv, d=d, S=4, W=70, dtype="bf16")
+    kw = _kw(g, hkv, d)
     pool = make_pool(**kw, cmax=9, max_sessions=n, n_blocks=n * 6)
     h = Harness(pool, n_sessions=n, **kw)
     pool.set_decode_kernel(kind)
     rnd = random.Random(g * 10 + n)
     for f in range(frames):
-        h.frame([rnd.randint(5, 9) for _ in range(n)], [rnd.randint(0, decodes) for _ in range(n)],
+        dec = [decodes if every else rnd.randint(0, decodes) for _ in range(n)]
+        h.frame([rnd.randint(5, 9) for _ in range(n)], dec,
                 n_split=(0, 2, 0, 5)[f % 4], check=f % 3 != 1)
     say(f"max err {h.max_err:.2e}")
 
@@ -48,12 +54,43 @@ def test_matrix_core_decode_head_dim_64_stores_what_the_append_stores(g):
         assert torch.equal(pools[0].kv, pools[1].kv), f"pool bytes differ after frame {f}"
 
 
-@pytest.mark.parametrize("g,n,d", [(1, 16, 128), (1, 17, 128), (2, 16, 128), (1, 32, 64),
-                                   (1, 33, 64)])
-def test_automatic_choice_around_its_line(g, n, d):
-    """16 and 17 (head dim 64: 32 and 33) sessions of 32 KV heads: two (four)
-    pairs per CU of 256, and one session more."""
-    _run(g, 32, n, 0, 3, 2, d)
+def _decode_outputs(g, hkv, n, d, kind):
+    """One decode of n sessions of 65 keys: (out, lse)."""
+    kw = _kw(g, hkv, d)
+    pool = make_pool(**kw, cmax=64, max_sessions=n, n_blocks=n * 10)
+    pool.set_decode_kernel(kind)
+    sids = [pool.session_open() for _ in range(n)]
+    gen = torch.Generator(device="cuda").manual_seed(g)
+    draw = lambda t, h: torch.randn((t, h, d), generator=gen, device="cuda").bfloat16()
+    pool.plan_begin(sids, [64] * n)
+    pool.frame_append_kv(0, draw(64 * n, hkv), draw(64 * n, hkv))
+    pool.plan_commit()
+    q, k, v = draw(n, hkv * g), draw(n, hkv), draw(n, hkv)
+    out, lse = torch.empty_like(q), torch.empty((n, hkv * g), dtype=torch.float32, device="cuda")
+    pool.plan_begin(sids, [1] * n)
+    pool.attend_decode_append(0, k, v, q, out, lse)
+    pool.plan_commit()
+    torch.cuda.synchronize()
+    return out, lse
+
+
+@pytest.mark.parametrize("past", [0, 1])
+@pytest.mark.parametrize("g,d", [(1, 128), (2, 128), (4, 128), (1, 64), (4, 64)])
+def test_automatic_choice_around_its_line(g, d, past):
+    """As many sessions of 32 KV heads as make two (head dim 64: four) pairs per
+    CU, which the matrix-core kernel takes, and one session more, which the
+    vector kernel takes: every session decodes in every round, and one launch is
+    bitwise that of the kernel expected and not that of the other one (the
+    matrix-core kernel can be forced at head dim 128 only)."""
+    hkv = 32
+    cu = torch.cuda.get_device_properties(0).multi_processor_count
+    n = (4 if d == 64 else 2) * cu // hkv + past
+    _run(g, hkv, n, 0, 3, 2, d, every=True)
+    auto = _decode_outputs(g, hkv, n, d, 0)
+    for kind in (1, 2) if d == 128 else (1,):
+        forced = _decode_outputs(g, hkv, n, d, kind)
+        same = torch.equal(auto[0], forced[0]) and torch.equal(auto[1], forced[1])
+        assert same == (kind == (1 if past else 2)), f"kernel {kind} forced against automatic"
 
 
 @pytest.mark.parametrize("dtype,d", [("bf16", 128), ("f32", 64)])
