@@ -414,8 +414,10 @@ def run_gpu(args, w):
     # pool bytes of one token (all kv heads): K and V rows, plus the two scale
     # exponent bytes per head of the fp8 cache
     n_dec, ms_dec = kt["decode"]
-    n_mrg, ms_mrg = kt["merge"]
+    # merges of decode segments; those of chunk segments belong to the prefill
+    n_mrg, ms_mrg = (x - y for x, y in zip(kt["merge"], kt["prefill_merge"]))
     n_pre, ms_pre = kt["prefill"]
+    ms_pre += kt["prefill_merge"][1]
     n_app, ms_app = kt["append"]
     vis = w.n_sink + w.window
     beta = Hkv * (2 * D + 2) if kvd == "fp8" else 2 * Hkv * D * esz
@@ -579,9 +581,9 @@ def run_call(args, w):
         acct["dec_n"] += kt["decode"][0]
         acct["dec_ms"] += kt["decode"][1]
         acct["pre_n"] += kt["prefill"][0]
-        acct["pre_ms"] += kt["prefill"][1]
+        acct["pre_ms"] += kt["prefill"][1] + kt["prefill_merge"][1]
         acct["app_ms"] += kt["append"][1]
-        acct["mrg_ms"] += kt["merge"][1]
+        acct["mrg_ms"] += kt["merge"][1] - kt["prefill_merge"][1]
         return kt["append"][0] > 0
     if args.kernel_times:
         pool.set_timing(True)

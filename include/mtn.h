@@ -372,10 +372,14 @@ mtn_status mtn_debug_inject_failure(mtn_pool *pool, int64_t launch_index);
 /* Per-kernel device timing.  When enabled, the library records HIP events
  * around each launch it makes and accumulates per-kernel-class totals;
  * mtn_pool_kernel_times synchronises those events and returns, for classes
- * 0 append, 1 prefill, 2 decode, 3 merge, the launch count and the summed
- * milliseconds (arrays of length >= 4), then resets the totals.               */
+ * 0 append, 1 prefill, 2 decode, 3 merge (of decode and of chunk-prefill
+ * segments), the launch count and the summed milliseconds (arrays of length
+ * >= 4), then resets the totals.  mtn_pool_prefill_merge_times returns the
+ * chunk prefill's share of class 3 in the last such call: it belongs to the
+ * prefill's time as the rest of the class does to the decode's.               */
 mtn_status mtn_pool_set_timing(mtn_pool *pool, int32_t enable);
 mtn_status mtn_pool_kernel_times(mtn_pool *pool, int64_t *launches, double *ms);
+mtn_status mtn_pool_prefill_merge_times(const mtn_pool *pool, int64_t *launches, double *ms);
 
 /* Plain device copy (dst = src, `bytes` a multiple of 16, both 16-byte
  * aligned): the bandwidth reference for the HBM roofline and the scale of the

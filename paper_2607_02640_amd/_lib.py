@@ -45,7 +45,7 @@ EXPORTS = [
     "mtn_attend_decode_append", "mtn_attend_decode_noalloc",
     "mtn_frame_step", "mtn_pool_stats", "mtn_session_info", "mtn_session_block_table",
     "mtn_plan_info", "mtn_debug_poison_dead", "mtn_pool_set_timing", "mtn_pool_set_prefill_pass_rows",
-    "mtn_pool_kernel_times", "mtn_hbm_copy", "mtn_hbm_read", "mtn_status_string", "mtn_pool_last_error",
+    "mtn_pool_kernel_times", "mtn_pool_prefill_merge_times", "mtn_hbm_copy", "mtn_hbm_read", "mtn_status_string", "mtn_pool_last_error",
     "mtn_pool_set_decode_kernel", "mtn_pool_last_split", "mtn_debug_inject_failure",
     "mtn_admission_create", "mtn_admission_destroy", "mtn_admission_offer",
     "mtn_admission_release", "mtn_admission_observe", "mtn_admission_get",
@@ -141,6 +141,7 @@ def load() -> C.CDLL:
         "mtn_pool_set_timing": (i32, [vp, i32]),
         "mtn_pool_set_prefill_pass_rows": (i32, [vp, i32]),
         "mtn_pool_kernel_times": (i32, [vp, P64, C.POINTER(C.c_double)]),
+        "mtn_pool_prefill_merge_times": (i32, [vp, P64, C.POINTER(C.c_double)]),
         "mtn_hbm_copy": (i32, [vp, vp, C.c_size_t, vp]),
         "mtn_hbm_read": (i32, [vp, C.c_size_t, vp]),
         "mtn_admission_create": (i32, [C.POINTER(AdmissionConfig), C.POINTER(vp)]),
@@ -370,7 +371,11 @@ class Pool:
         ms = (C.c_double * 4)()
         self._check(self.lib.mtn_pool_kernel_times(self.h, n, ms), "kernel_times")
         names = ("append", "prefill", "decode", "merge")
-        return {names[i]: (n[i], ms[i]) for i in range(4)}
+        times = {names[i]: (n[i], ms[i]) for i in range(4)}
+        # the chunk prefill's share of the merges
+        self._check(self.lib.mtn_pool_prefill_merge_times(self.h, n, ms), "kernel_times")
+        times["prefill_merge"] = (n[0], ms[0])
+        return times
 
 
 def hbm_copy(src, dst, nbytes: int, stream=None) -> None:

@@ -36,6 +36,8 @@ constexpr int kPfMaxSplit = 16;  // ... and key segments of a pass, at most
 // of a key segment, at least, and blocks that a split has to save its pass
 constexpr int kPfMinBlocksF32 = 2;
 constexpr int kPfMinSavedF32 = 12;
+// timing classes: append, prefill, decode, the decode's merge, the prefill's merge
+constexpr int kTimeClasses = 5;
 constexpr size_t kZeroPage = 2 * kBlock * 128 * 4;  // 16 KiB
 
 // Lowest-free-first block allocator over a bitmap (bit set = free).
@@ -162,10 +164,12 @@ struct mtn_pool {
 
     // timing
     bool timing = false;
-    std::vector<EventPair> ev_open[4];
+    std::vector<EventPair> ev_open[kTimeClasses];
     std::vector<hipEvent_t> ev_spare;
-    int64_t t_launch[4] = {};
-    double t_ms[4] = {};
+    int64_t t_launch[kTimeClasses] = {};
+    double t_ms[kTimeClasses] = {};
+    int64_t pf_merge_launch = 0;   // the chunk prefill's share of the merges that
+    double pf_merge_ms = 0.0;      // mtn_pool_kernel_times last returned
 
     std::string last_error;
 };
@@ -881,7 +885,7 @@ mtn_status prefill_impl(mtn_pool *P, int32_t layer, const void *q, void *out, fl
         st = timing_begin(P, s, &e0);
         if (st) return st;
         HIP_TRY(P, launch_merge(P->cfg.io_dtype, a, s));
-        st = timing_end(P, 3, e0, s);
+        st = timing_end(P, 4, e0, s);
         if (st) return st;
     }
     return MTN_OK;
@@ -1516,7 +1520,7 @@ mtn_status mtn_pool_set_timing(mtn_pool *P, int32_t enable) {
 mtn_status mtn_pool_kernel_times(mtn_pool *P, int64_t *launches, double *ms) {
     return guarded(P, [&]() -> mtn_status {
         if (!P || !launches || !ms) return MTN_ERR_INVALID_ARG;
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < kTimeClasses; ++c) {
             for (auto &pr : P->ev_open[c]) {
                 HIP_TRY(P, hipEventSynchronize(pr.b));
                 float t = 0.f;
@@ -1527,13 +1531,24 @@ mtn_status mtn_pool_kernel_times(mtn_pool *P, int64_t *launches, double *ms) {
                 P->ev_spare.push_back(pr.b);
             }
             P->ev_open[c].clear();
+        }
+        for (int c = 0; c < 4; ++c) {
             launches[c] = P->t_launch[c];
             ms[c] = P->t_ms[c];
-            P->t_launch[c] = 0;
-            P->t_ms[c] = 0.0;
         }
+        launches[3] += P->pf_merge_launch = P->t_launch[4];
+        ms[3] += P->pf_merge_ms = P->t_ms[4];
+        std::fill_n(P->t_launch, kTimeClasses, 0);
+        std::fill_n(P->t_ms, kTimeClasses, 0.0);
         return MTN_OK;
     });
+}
+
+mtn_status mtn_pool_prefill_merge_times(const mtn_pool *P, int64_t *launches, double *ms) {
+    if (!P || !launches || !ms) return MTN_ERR_INVALID_ARG;
+    *launches = P->pf_merge_launch;
+    *ms = P->pf_merge_ms;
+    return MTN_OK;
 }
 
 mtn_status mtn_hbm_read(const void *src, size_t bytes, void *stream) {

@@ -56,6 +56,22 @@ def test_split_prefill_matches_oracle(dtype, g, S, W, rows):
     say(f"max err {h.max_err:.2e}")
 
 
+def test_merge_times_tell_the_chunk_from_the_decode():
+    """One split chunk and two split decodes of two layers: class 3 holds the
+    merges of both, the chunk's share is told apart, and both reset."""
+    say("merge times")
+    pool, h = _setup("bf16", 16, 2, 4, 520, 60, 1, L=2)
+    for _ in range(9):
+        h.frame([60], [0], check=False)
+    pool.set_timing(True)
+    h.frame([60], [2], n_split=3)
+    t = pool.kernel_times()
+    assert (t["prefill"][0], t["decode"][0]) == (2, 4)
+    assert (t["merge"][0], t["prefill_merge"][0]) == (2 + 4, 2)
+    assert 0 < t["prefill_merge"][1] < t["merge"][1]
+    assert pool.kernel_times()["merge"] == pool.kernel_times()["prefill_merge"] == (0, 0.0)
+
+
 def test_many_ragged_passes_longest_first():
     """40 sessions x 8 KV heads: more passes than CUs, of mixed lengths."""
     say("longest first, 40 sessions")
