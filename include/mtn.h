@@ -353,10 +353,11 @@ mtn_status mtn_pool_set_prefill_pass_rows(mtn_pool *pool, int32_t rows);
 
 /* Test / tuning: the decode kernel.  0 (default) chooses by shape; 1 forces
  * the vector kernel (fp32 and bf16 pools); 2 forces the matrix-core kernel
- * (bf16 pools with head_dim 128; FP8 pools always use it).  Takes effect at
- * the next launch; results agree up to fp32 summation order.
- * MTN_ERR_UNSUPPORTED where the kernel does not exist for the pool,
- * MTN_ERR_BAD_STATE while a plan is open.                                    */
+ * (bf16 pools with head_dim 128; FP8 pools always use it; at head_dim 64 the
+ * automatic choice alone takes it).  Takes effect at the next launch; results
+ * agree up to fp32 summation order.  MTN_ERR_UNSUPPORTED where the kernel
+ * does not exist for the pool or cannot be forced, MTN_ERR_BAD_STATE while a
+ * plan is open.                                                              */
 mtn_status mtn_pool_set_decode_kernel(mtn_pool *pool, int32_t kind);
 
 /* Key segments (split) of the most recent decode launch of this pool.        */

@@ -735,7 +735,8 @@ AttnArgs attn_args(mtn_pool *P, int32_t layer, const void *q, void *out, float *
 // units 85.4 against 108.1, 1024 units 165.8 against 199.6; G = 4, 480 units
 // 42.5 against 48.8, 960 units 82.1 against 86.8, 2048 units 175 against 167;
 // G = 1, 960 units 81.6 against 84.1, 2048 units 172 against 162.
-// mtn_pool_set_decode_kernel can force either kernel where it exists.
+// mtn_pool_set_decode_kernel can force either kernel where it exists, the MFMA
+// one at head dim 128 only.
 bool use_mfma(const mtn_pool *P, int64_t units) {
     if (P->cfg.kv_dtype == MTN_FP8_E4M3) return true;
     if (P->cfg.kv_dtype != MTN_BF16 || !attn_mfma_bf16_supported(P->cfg.head_dim, P->G))
@@ -750,8 +751,8 @@ bool use_mfma(const mtn_pool *P, int64_t units) {
 // stay whole.  Otherwise they are split to fill one round, as far as that
 // shortens the launch by more than the merge and its partials cost:
 //   - while the segments have a CU each, down to 2 blocks per wave group;
-//   - past that, to 5 per wave group with the vector kernel (up to eight
-//     one-wave workgroups share a CU), 8 with the matrix-core one.
+//   - past that, to 5 per wave group with the vector kernel (up to four
+//     workgroups share a CU), 8 with the matrix-core one.
 // Measured per layer with the merge (C++ launches back to back): fp32 G = 4,
 // 13 sessions x 57 blocks 36.1 us at 3 segments, 26.0 at 11; one G = 1 session
 // x 129 blocks 19.2 at 8, 14.7 at 25; bf16 D = 64, two G = 8 sessions x 95
@@ -762,6 +763,12 @@ bool use_mfma(const mtn_pool *P, int64_t units) {
 // A split that saves a wave group fewer than 4 blocks' time is not taken: the
 // merge costs about 2 us, a block about 0.6 (one session x 20 blocks, G = 8:
 // 10.0 us unsplit, 11.1 at 2).
+// The blocks are those of a full window, also early in a call.  With the plan's
+// own blocks frames of 12 one-token rounds and 8 layers, the sessions at a tenth
+// of their window, were slower or alike: one bf16 session 1096 against 1057 us, 16
+// of them 2196 against 2188, 16 fp8 1837 against 1772, eight of G = 4 1895
+// against 1894 (at 13 keys: 1095 against 1058, 2034 against 2116, 1832 against
+// 1708, 1896 against 1893).
 int32_t auto_split(const mtn_pool *P, int32_t n_items) {
     const int64_t units = std::max<int64_t>((int64_t)n_items * P->cfg.n_kv_heads, 1);
     const int64_t max_keys = P->unbounded ? P->cfg.max_len : (int64_t)P->S + P->W;
@@ -1491,7 +1498,7 @@ mtn_status mtn_pool_set_decode_kernel(mtn_pool *P, int32_t kind) {
         if (kind == 2 && c.kv_dtype == MTN_F32)
             return fail(P, MTN_ERR_UNSUPPORTED, "fp32 pools have no matrix decode kernel");
         if (kind == 2 && (c.head_dim != 128 || !attn_mfma_bf16_supported(c.head_dim, P->G)))
-            return fail(P, MTN_ERR_UNSUPPORTED, "no matrix decode kernel for this shape");
+            return fail(P, MTN_ERR_UNSUPPORTED, "the matrix decode kernel can be forced at head_dim 128 only");
         P->decode_kernel = kind;
         return MTN_OK;
     });
