@@ -634,24 +634,28 @@ static __device__ __align__(256) float scratch[kScratchFloats];
 // lane.  Bound by memory round trips: one, with the output row loaded beside
 // the partials, for up to CH splits.  One session's frame, 768 merges of 32
 // splits, took 10.07 ms with rounds of eight splits and the row after them,
-// 9.69 ms so; at four splits (32 fp8 sessions) 4.959 against 4.941 ms.
+// 9.69 ms so; at four splits the two are alike.
 template <typename T, int D, int CH>
 __global__ __launch_bounds__(64) void k_merge(AttnArgs a) {
     constexpr int VD = D / 64;  // output dims per lane
     const int64_t th = blockIdx.x;  // t * Hq + hq
     const int lane = threadIdx.x;
     const int ns = a.n_split;       // 2 .. 64
-    const float *pacc = a.part + th * ns * D + lane * VD;
+    const float *pacc = a.part + th * ns * D;
     const float *pml = a.part + (int64_t)a.p.n_tok * a.g.hq * ns * D + th * ns * 2;
     float acc[VD];
 #pragma unroll
     for (int r = 0; r < VD; ++r) acc[r] = 0.f;
     float part[CH][VD];
+    // (past ns: zeros, of weight 0; a split's own sums may be infinite, and 0 * Inf
+    // is NaN)
     auto load = [&](int s0) {
 #pragma unroll
-        for (int c = 0; c < CH; ++c)
+        for (int c = 0; c < CH; ++c) {
+            const float *src = s0 + c < ns ? pacc + (s0 + c) * D : (const float *)a.zero_page;
 #pragma unroll
-            for (int r = 0; r < VD; ++r) part[c][r] = pacc[min(s0 + c, ns - 1) * D + r];  // past ns: unused
+            for (int r = 0; r < VD; ++r) part[c][r] = src[lane * VD + r];
+        }
     };
     load(0);
     const float2 ml0 = *(const float2 *)(pml + 2 * min(lane, ns - 1));  // lanes past ns: unused
@@ -671,7 +675,7 @@ __global__ __launch_bounds__(64) void k_merge(AttnArgs a) {
         if (s0) load(s0);
 #pragma unroll
         for (int c = 0; c < CH; ++c) {
-            // no branch: a split past ns weighs 0 (its slot repeats a finite partial)
+            // no branch: a split past ns weighs 0
             const float wl = __builtin_bit_cast(
                 float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), min(s0 + c, 63)));
             const float ws = s0 + c < ns ? wl : 0.f;
