@@ -769,7 +769,7 @@ __global__ __launch_bounds__(64 * kReadWaves) void k_read(const uint8_t *__restr
 // MFMA chunk prefill (bf16 pool, D = 128 or 64; fp8 pool, D = 128): one
 // workgroup per (sequence, row pass, kv head, key segment).  (At D = 64 bf16 chunks the
 // vector kernel, which reads the window once per token, took 76 us a layer for
-// 21 sessions of 9 .. 33 tokens over 1500 keys at G = 8; this one 17 + 4.6.)
+// 21 sessions of 9 .. 33 tokens over 1500 keys at G = 8; this one 20 + 3.)
 // ---------------------------------------------------------------------------
 // Rows of the chunk are (token j, group head g) -> r = j * G + g, in tiles of
 // 16.  Keys stream in stages of 32 (two 16-token blocks) through LDS.

@@ -44,7 +44,7 @@ def test_random_configuration_against_oracle(seed):
     if kernel == 1 and c["dtype"] == "fp8":
         kernel = 0   # the FP8 cache has no vector decode kernel
     if kernel == 2 and not (c["dtype"] in ("bf16", "fp8") and c["d"] == 128):
-        kernel = 0   # the matrix decode kernel needs a bf16 / fp8 pool with D = 128
+        kernel = 0   # the matrix decode kernel can be forced at D = 128 only
     if kernel:
         pool.set_decode_kernel(kernel)
     h = Harness(pool, n_sessions=c["n"], n_layers=2, hq=c["hkv"] * c["g"], hkv=c["hkv"],
