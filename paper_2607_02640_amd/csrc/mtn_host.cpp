@@ -376,59 +376,103 @@ int64_t keys_seen(const mtn_pool *P, int64_t t0, int64_t t1) {
            std::max<int64_t>(0, t1 - std::max<int64_t>(P->S, t0 - P->W + 1) + 1);
 }
 
+// Microseconds that a chunk-prefill workgroup of the bf16 / fp8 kernel takes to
+// start and end, and per stage of two blocks, with `rpp` query rows per pass; and
+// those that cutting the passes into segments adds: the merge's launch, its one
+// wave per output row, and the partial rows written and read (see plan_prefill).
+struct PfCost {
+    double start, stage;
+};
+PfCost pf_cost(const mtn_pool *P, int64_t rpp) {
+    const bool wide = rpp > 128, fp8 = P->cfg.kv_dtype == MTN_FP8_E4M3;
+    if (P->cfg.head_dim == 64) return wide ? PfCost{8.0, 0.73} : PfCost{7.0, 0.39};
+    return wide ? PfCost{10.5, fp8 ? 0.85 : 0.57} : PfCost{9.0, fp8 ? 0.97 : 0.46};
+}
+double pf_merge_cost(int64_t rows, int64_t part_floats) {
+    return 3.0 + 0.2e-3 * (double)rows + 0.28e-6 * 4.0 * (double)part_floats;
+}
+
 // The chunk prefill's launch: query rows per pass, key segments per pass, one
 // record per (sequence, row pass), longest first.
 //
 // A workgroup streams its keys at the pace of one CU, so a launch with fewer
 // workgroups than CUs leaves the rest idle: its passes' keys are then cut into
-// segments until the CUs are filled, at least kPfMinStages stages each and at
-// most kPfMaxSplit (more and the partial rows cost what the shorter segments
-// gain).  Per layer with the merge, one session of 25 tokens over 4100 keys
-// at G = 8 (4 passes of 256 rows or 8 of 128): 70.4 us unsplit, 27.9 at 4
-// segments, 19.1 at 16, 21.0 at 32; 16 sessions 73.4 us (128-row passes,
-// unsplit) against 47.7 (256-row, 4 segments); 32 fp8 sessions 117.0 against
-// 94.2 (256-row, 2 segments); one session over 600 keys 20.0 against 15.4 at
-// 4 segments and 17.3 at 2.
-// The fp32 kernel's blocks take longer, so its segments go down to two of them,
-// but a short window is not split for less than the merge and its launch cost
+// segments, at most what fills the CUs and kPfMaxSplit, of at least kPfMinStages
+// stages.  Passes of 128 rows make more workgroups but read every key twice as
+// often.  Which of these is fastest depends on what the segments save against
+// the merge, whose partial rows grow with the chunk's rows, so the plan takes the
+// smallest estimate of pf_cost and pf_merge_cost (fitted to 38 shapes of 1 to 32
+// sessions, 300 to 4100 keys and 4 to 2000 tokens, both pass sizes, 1 to 16
+// segments; its choices are within 12 % of the best measured one where
+// 128-row passes are considered).  Per layer with the merge: one session of 25
+// tokens over 4100 keys at G = 8, 70.3 us unsplit, 19.3 at 16 segments of
+// 128-row passes (90.5 and 22.3 with 256); 16 sessions 87.9 unsplit, 57.3 at two
+// segments of 128-row passes, 48.8 at four of 256; 32 fp8 sessions 141.4 unsplit,
+// 94.1 at two of 256.  A 961-token chunk alone (G = 4, 8 kv heads) 24.7 unsplit
+// with 128-row passes, 38.8 at two segments of 256, which filling the CUs alone
+// would choose; 16 sessions of 25 tokens over 404 keys 18.3 and 25.7.
+// 128 rows are considered where 256-row passes fill at most half the CUs.
+//
+// The fp32 kernel has one pass size.  Its blocks take longer, so its segments go
+// down to two of them and fill the CUs, but a short window is not split for less
+// than the merge and its launch cost
 // (two-layer frames of 6 sessions, G = 2, D = 128, 18 blocks: 103.1 us at 2
 // segments, 91.9 at 4, 87.0 at 9; layer calls over 10 blocks at D = 64: 47.5
 // unsplit, 52.9 at 5).
-// 128-row passes make more workgroups but read every key twice as often: they
-// pay only while the split cannot fill the CUs about twice over (one session
-// 19.1 against 22.3 us with 256, four 27.0 against 29.0; sixteen lose, 57.3
-// against 47.7).
 //
 // Longest first: with more workgroups than CUs the CUs that end early take the
 // next pass.  A 4100-token chunk's 516 causal passes in ascending order end
 // with the longest ones (measured per layer: 176 us; descending, 149 us).
 void plan_prefill(mtn_pool *P) {
     const int32_t n_seq = P->n_seq;
-    const bool mfma = prefill_mfma_supported(P->cfg.kv_dtype, P->cfg.head_dim, P->G);
     auto passes = [&](int64_t rpp) {
         int64_t n = 0;
         for (int32_t i = 0; i < n_seq; ++i) n += ceil_div((int64_t)P->seq_ntok[i] * P->G, rpp);
         return n * P->cfg.n_kv_heads;
     };
-    int64_t blocks = 0;  // of the longest sequence
-    for (int32_t i = 0; i < n_seq; ++i)
-        blocks = std::max(blocks, ceil_div(keys_seen(P, P->seq_pos0[i], P->seq_pos0[i] + P->seq_ntok[i] - 1),
-                                           kBlock));
-    const bool f32 = P->cfg.kv_dtype == MTN_F32;  // its kernel has one pass size
-    const int64_t min_blocks = f32 ? kPfMinBlocksF32 : 2 * kPfMinStages;
-    const int64_t max_split = std::max<int64_t>(1, std::min<int64_t>(blocks / min_blocks, kPfMaxSplit));
+    auto blocks = [&](int64_t tokens) {  // that the longest pass of `tokens` tokens sees
+        int64_t n = 0;
+        for (int32_t i = 0; i < n_seq; ++i) {
+            const int64_t t1 = P->seq_pos0[i] + P->seq_ntok[i] - 1;
+            n = std::max(n, ceil_div(keys_seen(P, std::max(P->seq_pos0[i], t1 - tokens + 1), t1), kBlock));
+        }
+        return n;
+    };
+    const bool f32 = P->cfg.kv_dtype == MTN_F32;
+    const int64_t out_rows = (int64_t)P->T * P->cfg.n_q_heads;
+    const int64_t per = out_rows * (P->cfg.head_dim + 2);  // floats of a segment's partial rows
     int64_t rpp = f32 ? prefill_f32_rows_per_pass()
                       : P->pf_rows_cfg ? P->pf_rows_cfg : prefill_rows_per_pass();
-    if (!f32 && !P->pf_rows_cfg && P->n_cu > 0 && prefill_pass_rows_valid(128) &&
-        2 * passes(rpp) <= P->n_cu && passes(128) * max_split <= 2 * (int64_t)P->n_cu)
-        rpp = 128;
-    P->pf_rows = (int32_t)rpp;
     P->pf_split = 1;
-    if (mfma && P->n_cu > 0) {
-        const int64_t per = (int64_t)P->T * P->cfg.n_q_heads * (P->cfg.head_dim + 2);  // floats of a segment
-        const int64_t ns = std::min<int64_t>({P->n_cu / passes(rpp), max_split, (int64_t)P->part_floats / per});
-        if (ns > 1 && !(f32 && blocks - blocks / ns < kPfMinSavedF32)) P->pf_split = (int32_t)ns;
+    if (P->n_cu > 0 && f32) {
+        const int64_t n = blocks(P->cfg.max_chunk);
+        const int64_t ns = std::min<int64_t>({P->n_cu / passes(rpp), n / kPfMinBlocksF32, kPfMaxSplit,
+                                              (int64_t)P->part_floats / per});
+        if (ns > 1 && n - n / ns >= kPfMinSavedF32) P->pf_split = (int32_t)ns;
+    } else if (P->n_cu > 0) {
+        const int64_t full = rpp;
+        double best = 0.0;
+        for (const int64_t rows : {full, (int64_t)128}) {
+            const int64_t np = passes(rows);
+            if (rows != full && (P->pf_rows_cfg || !prefill_pass_rows_valid((int)rows) ||
+                                 2 * passes(full) > P->n_cu))
+                continue;
+            const int64_t stages = ceil_div(blocks(ceil_div(rows, P->G)), 2);
+            const int64_t top = std::min<int64_t>({P->n_cu / np, stages / kPfMinStages, kPfMaxSplit,
+                                                   (int64_t)P->part_floats / per});
+            const PfCost c = pf_cost(P, rows);
+            for (int64_t ns = 1; ns == 1 || ns <= top; ++ns) {
+                const double t = c.start + c.stage * (double)ceil_div(stages, ns) +
+                                 (ns > 1 ? pf_merge_cost(out_rows, ns * per) : 0.0);
+                if ((rows == full && ns == 1) || t < best) {
+                    best = t;
+                    rpp = rows;
+                    P->pf_split = (int32_t)ns;
+                }
+            }
+        }
     }
+    P->pf_rows = (int32_t)rpp;
     // one record per (sequence, row pass) with everything its workgroup
     // needs before the first copy, so that it takes one metadata load.
     // The prefill takes io row (row of t0) + j for token t0 + j: plans

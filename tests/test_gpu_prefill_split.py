@@ -56,6 +56,32 @@ def test_split_prefill_matches_oracle(dtype, g, S, W, rows):
     say(f"max err {h.max_err:.2e}")
 
 
+@pytest.mark.parametrize("W,n,c,split", [
+    (None, 1, 700, False),   # a long chunk's partial rows cost more than the segments save
+    (400, 16, 25, False),    # so do those of many sessions over a short window
+    (None, 1, 60, False),    # two stages: nothing to cut
+    (2000, 2, 25, True),     # few rows over a long window
+])
+def test_segments_are_cut_where_they_save_more_than_the_merge_costs(W, n, c, split):
+    say(f"prefill split W={W} sessions={n} chunk={c}")
+    kw = dict(n_layers=1, hq=32, hkv=8, d=128, S=0, W=W, dtype="bf16")
+    blocks = n * -(-((W or 0) + c + 31) // 16)
+    pool = make_pool(**kw, cmax=c, max_sessions=n, n_blocks=blocks, max_len=0 if W else c)
+    sids = [pool.session_open() for _ in range(n)]
+    q = torch.zeros((n * c, 32, 128), dtype=torch.bfloat16, device="cuda")
+    k, o = torch.zeros((n * c, 8, 128), dtype=torch.bfloat16, device="cuda"), torch.empty_like(q)
+    for _ in range(-(-(W or 0) // c)):
+        pool.plan_begin(sids, [c] * n)
+        pool.frame_append_kv(0, k, k)
+        pool.plan_commit()
+    pool.set_timing(True)
+    pool.plan_begin(sids, [c] * n)
+    pool.frame_append_kv(0, k, k)
+    pool.attend_chunk_prefill(0, q, o)
+    pool.plan_commit()
+    assert (pool.kernel_times()["prefill_merge"][0] == 1) == split
+
+
 def test_merge_times_tell_the_chunk_from_the_decode():
     """One split chunk and two split decodes of two layers: class 3 holds the
     merges of both, the chunk's share is told apart, and both reset."""
