@@ -1193,9 +1193,12 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
         // How far a score may exceed the reference (log2 units) before it moves.
         // At 0, D = 64, the reference is the running maximum and the largest
         // probability 1, exact in bf16, as the vector kernel had it: with 2^8 the
-        // outputs' error was 2-3 % larger (frames of 21 sessions 404 against 414 us).
+        // outputs' error was 2-3 % larger.  It costs the rescales: frames of 21
+        // sessions 404 against 407 us, chunks of 64 sessions over 2000 keys 213
+        // against 253, 4000 causal tokens 110 against 132 (the vector kernel 2124
+        // and 1306).
         constexpr float kLazy = D == 64 ? 0.f : 8.f;
-        // bf16 pool: the QK MFMAs start their accumulators at -msh, so the
+        // bf16, D = 128: the QK MFMAs start their accumulators at -msh, so the
         // scores come out already shifted by the reference and each
         // probability is one exponential with no subtraction; thr is the bump
         // threshold on shifted scores (m_ref - msh + 2^8: 2^8 once the first
@@ -1203,7 +1206,10 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
         // scores (msh stays 0, thr = m_ref + 2^8): its conversion stage leaves
         // no registers for the four shift values per tile (measured 0.386 ->
         // 0.495 ms per layer with them, from spills inside the stage loops).
-        constexpr bool kShift = !F8;
+        // So does D = 64, whose reference moves too often for the shift to pay
+        // (chunks of 64 sessions over 2000 keys 260 us a layer call of four with
+        // it, 253 without; 4000 causal tokens 138 and 132).
+        constexpr bool kShift = !F8 && D == 128;
         float msh[kPfTpw], thr[kPfTpw];
         f32x4_t csh[kPfTpw];  // {-msh} x 4, kept so the QK start needs no moves
         constexpr bool kMfmaSum = !F8 && D == 128;
@@ -1495,9 +1501,11 @@ __global__ __launch_bounds__(64 * kPfWaves) void k_prefill_mfma(PfArgs pa) {
                               vmax3(sb[i][2], sb[i][3], sa[i][0]));
                 bump = bump || m8[i] > thr[i];
             }
-            if (__builtin_amdgcn_ballot_w64(bump)) {
+            // (D = 64, whose references move in most stages: a test for each tile)
+            if (D == 64 || __builtin_amdgcn_ballot_w64(bump)) {
 #pragma unroll
                 for (int i = 0; i < NT; ++i) {
+                    if (D == 64 && !__builtin_amdgcn_ballot_w64(m8[i] > thr[i])) continue;
                     // true row max of the stage, the new reference, and the
                     // re-shift of this stage's (already shifted) scores
                     const float mx = rows_max(m8[i]) + msh[i];

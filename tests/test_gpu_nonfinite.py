@@ -103,3 +103,41 @@ def test_a_bad_key_or_value_stays_with_the_rows_that_see_it(dtype, d, g, S, W, r
                             assert (out[sees][..., dim] == x).all(), f"{what}, dim {dim}"
                 if dtype != "fp8":  # (the row's scale may differ without those elements)
                     assert torch.equal(out[sees][..., ~dims], clean[0][sees][..., ~dims]), what
+
+
+def test_a_bad_value_of_a_fused_chunk_stays_with_the_rows_that_see_it():
+    """The fp8 frame whose chunk prefill stores the chunk itself: the tiles that
+    are computed once more read the tokens that this launch has stored."""
+    say("non-finite values, fused fp8 chunk")
+    hkv, g, d, W, n = 4, 4, 128, 60, 40
+    # enough one-pass sequences that the prefill is not split and carries the append
+    ns = torch.cuda.get_device_properties(0).multi_processor_count // (2 * hkv) + 2
+    kw = dict(n_layers=1, hq=hkv * g, hkv=hkv, d=d, S=4, W=W, dtype="fp8")
+    outs = []
+    for bad in (None, 0, 17, n - 1):
+        pool = make_pool(**kw, cmax=n, max_sessions=ns, n_blocks=ns * 8)
+        sids = [pool.session_open() for _ in range(ns)]
+        gen = torch.Generator(device="cuda").manual_seed(8)
+        draw = lambda h: torch.randn((1, ns * n, h, d), generator=gen, device="cuda").bfloat16()
+        pool.set_timing(True)
+        frames = []
+        for f in range(3):
+            q, k, v = draw(hkv * g), draw(hkv), draw(hkv)
+            if bad is not None and f != 1:
+                v.view(ns, n, hkv, d)[:, bad, :, 5] = float("nan")
+            o = torch.empty_like(q)
+            pool.frame_step(sids, [n] * ns, [0] * ns, q, k, v, o)
+            frames.append(o.view(ns, n, hkv * g, d))
+        torch.cuda.synchronize()
+        assert pool.kernel_times()["append"][0] == 0, "the frames did not fuse the append"
+        outs.append(frames)
+        if bad is None:
+            continue
+        for f in range(3):
+            t = torch.arange(f * n, (f + 1) * n)
+            sees = torch.zeros(n, dtype=torch.bool)
+            for p in (bad, 2 * n + bad):  # frames 0 and 2 bring a bad value
+                sees |= (p <= t) & ((t < p + W) | (p < kw["S"]))
+            got, clean = frames[f], outs[0][f]
+            assert torch.equal(got[:, ~sees], clean[:, ~sees]), f"bad {bad}, frame {f}"
+            assert torch.isnan(got[:, sees][..., 5]).all(), f"bad {bad}, frame {f}"
