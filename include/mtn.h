@@ -344,11 +344,12 @@ mtn_status mtn_debug_poison_dead(mtn_pool *pool, void *stream);
 
 /* Tuning: query rows per chunk-prefill pass (rows are token x G + group head;
  * each pass of each kv head is one workgroup that reads the keys its rows can
- * see).  0 (the default) chooses per plan: 256, or 128 for the smallest
- * batches; 128 or 256 fix it.  A plan whose passes leave compute units idle
- * also cuts each pass's keys into segments, merged by log-sum-exp as the
- * decode's are.  Takes effect at the next mtn_plan_begin.  Results are the
- * same either way up to fp32 summation order.  Other values: MTN_ERR_INVALID_ARG.            */
+ * see).  0 (the default) chooses per plan: 256, or 128 for small batches;
+ * 128 or 256 fix it.  A plan whose passes leave compute units idle also cuts
+ * each pass's keys into segments where that saves more than merging them (by
+ * log-sum-exp, as the decode's are) costs.  Takes effect at the next
+ * mtn_plan_begin.  Results are the same either way up to fp32 summation order.
+ * Other values: MTN_ERR_INVALID_ARG.                                         */
 mtn_status mtn_pool_set_prefill_pass_rows(mtn_pool *pool, int32_t rows);
 
 /* Test / tuning: the decode kernel.  0 (default) chooses by shape; 1 forces

@@ -32,10 +32,11 @@ constexpr int kSmallSlots = 16;
 constexpr int32_t kSmallWords = 2048;
 constexpr int kPfMinStages = 4;  // chunk prefill: stages (two blocks) of a key segment, at least
 constexpr int kPfMaxSplit = 16;  // ... and key segments of a pass, at most
-// fp32 chunk prefill, whose stages are single blocks of 0.5 to 0.9 us: blocks
-// of a key segment, at least, and blocks that a split has to save its pass
+// fp32 chunk prefill, whose stages are single blocks: blocks of a key segment, at
+// least, and microseconds that segments have to save (the merge is one more
+// launch for the host, too)
 constexpr int kPfMinBlocksF32 = 2;
-constexpr int kPfMinSavedF32 = 12;
+constexpr double kPfMinSavedF32 = 3.0;
 // timing classes: append, prefill, decode, the decode's merge, the prefill's merge
 constexpr int kTimeClasses = 5;
 constexpr size_t kZeroPage = 2 * kBlock * 128 * 4;  // 16 KiB
@@ -376,8 +377,8 @@ int64_t keys_seen(const mtn_pool *P, int64_t t0, int64_t t1) {
            std::max<int64_t>(0, t1 - std::max<int64_t>(P->S, t0 - P->W + 1) + 1);
 }
 
-// Microseconds that a chunk-prefill workgroup of the bf16 / fp8 kernel takes to
-// start and end, and per stage of two blocks, with `rpp` query rows per pass; and
+// Microseconds that a chunk-prefill workgroup takes to start and end, and per
+// stage (two blocks; fp32: one), with `rpp` query rows per pass (fp32: 64); and
 // those that cutting the passes into segments adds: the merge's launch, its one
 // wave per output row, and the partial rows written and read (see plan_prefill).
 struct PfCost {
@@ -385,6 +386,7 @@ struct PfCost {
 };
 PfCost pf_cost(const mtn_pool *P, int64_t rpp) {
     const bool wide = rpp > 128, fp8 = P->cfg.kv_dtype == MTN_FP8_E4M3;
+    if (P->cfg.kv_dtype == MTN_F32) return P->cfg.head_dim == 64 ? PfCost{6.2, 0.71} : PfCost{9.5, 1.17};
     if (P->cfg.head_dim == 64) return wide ? PfCost{8.0, 0.73} : PfCost{7.0, 0.39};
     return wide ? PfCost{10.5, fp8 ? 0.85 : 0.57} : PfCost{9.0, fp8 ? 0.97 : 0.46};
 }
@@ -414,11 +416,12 @@ double pf_merge_cost(int64_t rows, int64_t part_floats) {
 // 128 rows are considered where 256-row passes fill at most half the CUs.
 //
 // The fp32 kernel has one pass size.  Its blocks take longer, so its segments go
-// down to two of them and fill the CUs, but a short window is not split for less
-// than the merge and its launch cost
-// (two-layer frames of 6 sessions, G = 2, D = 128, 18 blocks: 103.1 us at 2
-// segments, 91.9 at 4, 87.0 at 9; layer calls over 10 blocks at D = 64: 47.5
-// unsplit, 52.9 at 5).
+// down to two of them, but a short window is not split for less than
+// kPfMinSavedF32 (fitted to 96 shapes of 1 to 20 sessions, 9 to 95 blocks;
+// two-layer frames of 6 sessions, G = 2, D = 128, 18 blocks: 103.1 us at 2
+// segments, 91.9 at 4, 87.0 at 9; 150 causal tokens, 10 blocks, G = 1, D = 128:
+// 21.0 unsplit, 16.0 at 5, and the vector kernel 13.3; layer calls over 10 blocks
+// at D = 64: 47.5 unsplit, 52.9 at 5).
 //
 // Longest first: with more workgroups than CUs the CUs that end early take the
 // next pass.  A 4100-token chunk's 516 causal passes in ascending order end
@@ -444,26 +447,24 @@ void plan_prefill(mtn_pool *P) {
     int64_t rpp = f32 ? prefill_f32_rows_per_pass()
                       : P->pf_rows_cfg ? P->pf_rows_cfg : prefill_rows_per_pass();
     P->pf_split = 1;
-    if (P->n_cu > 0 && f32) {
-        const int64_t n = blocks(P->cfg.max_chunk);
-        const int64_t ns = std::min<int64_t>({P->n_cu / passes(rpp), n / kPfMinBlocksF32, kPfMaxSplit,
-                                              (int64_t)P->part_floats / per});
-        if (ns > 1 && n - n / ns >= kPfMinSavedF32) P->pf_split = (int32_t)ns;
-    } else if (P->n_cu > 0) {
+    if (P->n_cu > 0) {
         const int64_t full = rpp;
         double best = 0.0;
         for (const int64_t rows : {full, (int64_t)128}) {
             const int64_t np = passes(rows);
-            if (rows != full && (P->pf_rows_cfg || !prefill_pass_rows_valid((int)rows) ||
+            if (rows != full && (f32 || P->pf_rows_cfg || !prefill_pass_rows_valid((int)rows) ||
                                  2 * passes(full) > P->n_cu))
                 continue;
-            const int64_t stages = ceil_div(blocks(ceil_div(rows, P->G)), 2);
-            const int64_t top = std::min<int64_t>({P->n_cu / np, stages / kPfMinStages, kPfMaxSplit,
-                                                   (int64_t)P->part_floats / per});
+            const int64_t stages = ceil_div(blocks(ceil_div(rows, P->G)), f32 ? 1 : 2);
+            const int64_t top = std::min<int64_t>({P->n_cu / np, stages / (f32 ? kPfMinBlocksF32 : kPfMinStages),
+                                                   kPfMaxSplit, (int64_t)P->part_floats / per});
             const PfCost c = pf_cost(P, rows);
+            const double whole = c.start + c.stage * (double)stages;  // in one segment
             for (int64_t ns = 1; ns == 1 || ns <= top; ++ns) {
-                const double t = c.start + c.stage * (double)ceil_div(stages, ns) +
-                                 (ns > 1 ? pf_merge_cost(out_rows, ns * per) : 0.0);
+                const double t = ns == 1 ? whole
+                                         : c.start + c.stage * (double)ceil_div(stages, ns) +
+                                               pf_merge_cost(out_rows, ns * per);
+                if (f32 && ns > 1 && t > whole - kPfMinSavedF32) continue;
                 if ((rows == full && ns == 1) || t < best) {
                     best = t;
                     rpp = rows;

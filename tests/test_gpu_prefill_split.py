@@ -56,20 +56,23 @@ def test_split_prefill_matches_oracle(dtype, g, S, W, rows):
     say(f"max err {h.max_err:.2e}")
 
 
-@pytest.mark.parametrize("W,n,c,split", [
-    (None, 1, 700, False),   # a long chunk's partial rows cost more than the segments save
-    (400, 16, 25, False),    # so do those of many sessions over a short window
-    (None, 1, 60, False),    # two stages: nothing to cut
-    (2000, 2, 25, True),     # few rows over a long window
+@pytest.mark.parametrize("dtype,g,d,W,n,c,split", [
+    ("bf16", 4, 128, None, 1, 700, False),  # a long chunk's partial rows cost more than the segments save
+    ("bf16", 4, 128, 400, 16, 25, False),   # so do those of many sessions over a short window
+    ("bf16", 4, 128, None, 1, 60, False),   # two stages: nothing to cut
+    ("bf16", 4, 128, 2000, 2, 25, True),    # few rows over a long window
+    ("f32", 1, 128, 128, 1, 25, True),      # ten slow blocks
+    ("f32", 1, 64, 128, 1, 25, False),      # ten that cost about a merge and its launch
 ])
-def test_segments_are_cut_where_they_save_more_than_the_merge_costs(W, n, c, split):
-    say(f"prefill split W={W} sessions={n} chunk={c}")
-    kw = dict(n_layers=1, hq=32, hkv=8, d=128, S=0, W=W, dtype="bf16")
+def test_segments_are_cut_where_they_save_more_than_the_merge_costs(dtype, g, d, W, n, c, split):
+    say(f"prefill split {dtype} G={g} d={d} W={W} sessions={n} chunk={c}")
+    kw = dict(n_layers=1, hq=8 * g, hkv=8, d=d, S=0, W=W, dtype=dtype)
+    io = torch.float32 if dtype == "f32" else torch.bfloat16
     blocks = n * -(-((W or 0) + c + 31) // 16)
     pool = make_pool(**kw, cmax=c, max_sessions=n, n_blocks=blocks, max_len=0 if W else c)
     sids = [pool.session_open() for _ in range(n)]
-    q = torch.zeros((n * c, 32, 128), dtype=torch.bfloat16, device="cuda")
-    k, o = torch.zeros((n * c, 8, 128), dtype=torch.bfloat16, device="cuda"), torch.empty_like(q)
+    q = torch.zeros((n * c, 8 * g, d), dtype=io, device="cuda")
+    k, o = torch.zeros((n * c, 8, d), dtype=io, device="cuda"), torch.empty_like(q)
     for _ in range(-(-(W or 0) // c)):
         pool.plan_begin(sids, [c] * n)
         pool.frame_append_kv(0, k, k)
